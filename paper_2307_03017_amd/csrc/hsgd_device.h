@@ -82,6 +82,94 @@ __device__ __forceinline__ Taps make_taps(const hsgd_warp& wp, int x, int y, int
     return t;
 }
 
+// ------------------------------------------------------------------------------------
+// positions under a general homography, one row of pixels at a time
+// ------------------------------------------------------------------------------------
+// The homogeneous position of pixel x of a fixed row y: q_i = a_i x + b_i, the products of y
+// taken once per row (the same FP64 operations in the same order as for a single pixel).
+// A translation record is the map x + ix + fx, y + iy + fy.
+struct RowMap {
+    double a0, a1, a2, b0, b1, b2;
+};
+__device__ __forceinline__ RowMap row_map(const hsgd_warp& w, int y) {
+    const double yd = (double)y;
+    if (w.is_shift) return RowMap{1.0, 0.0, 0.0, (double)w.ix + (double)w.fx, yd + (double)w.iy + (double)w.fy, 1.0};
+    return RowMap{w.G[0], w.G[3], w.G[6], __builtin_fma(w.G[1], yd, w.G[2]), __builtin_fma(w.G[4], yd, w.G[5]),
+                  __builtin_fma(w.G[7], yd, w.G[8])};
+}
+
+// 1 / q to FP64 accuracy: the hardware's estimate and two Newton steps (its ~24 correct bits
+// become 48 and then the 53 of the format). An IEEE division costs three times as many
+// instructions and its last-bit rounding moves a position by 1e-13 pixels.
+__device__ __forceinline__ double rcp_f64(double q) {
+    double r = __builtin_amdgcn_rcp(q);
+    r = __builtin_fma(__builtin_fma(-q, r, 1.0), r, r);
+    return __builtin_fma(__builtin_fma(-q, r, 1.0), r, r);
+}
+
+// Position (floor and fraction, FP64 until the fraction is rounded) of pixel x of the row.
+struct MapPos {
+    double fu, fv;     // floor of the position; anything when the point is not in front
+    float fx, fy;
+    bool front;
+};
+__device__ __forceinline__ MapPos map_pos(const RowMap& m, double x) {
+    const double q2 = __builtin_fma(m.a2, x, m.b2);
+    const double r = rcp_f64(q2);
+    const double u = __builtin_fma(m.a0, x, m.b0) * r, v = __builtin_fma(m.a1, x, m.b1) * r;
+    MapPos p;
+    p.fu = floor(u);
+    p.fv = floor(v);
+    p.fx = (float)(u - p.fu);
+    p.fy = (float)(v - p.fv);
+    p.front = q2 > 0.0;
+    return p;
+}
+
+// Byte offsets of the four taps in a W x H plane of S-byte pixels, for loads through a buffer
+// resource over the plane: a tap outside it gets an offset past the resource and reads 0, the
+// zero padding. A wave whose lanes all have the four taps inside (nearly every wave) takes
+// the short way: one address, the others at fixed distances. When no tap of a lane is inside,
+// its fractions (which may be NaN there) become 0.
+constexpr unsigned kOutside = 0xfffffff0u;
+struct TapOffs {
+    unsigned o00, o10, o01, o11;
+};
+// FP64 -> int32 in one instruction: out-of-range values saturate, NaN gives 0.
+__device__ __forceinline__ int cvt_i32_f64(double d) {
+    int i;
+    asm("v_cvt_i32_f64 %0, %1" : "=v"(i) : "v"(d));
+    return i;
+}
+template <int S>
+__device__ __forceinline__ TapOffs tap_offsets(MapPos& p, int W, int H) {
+    TapOffs t;
+    int x0 = cvt_i32_f64(p.fu), y0 = cvt_i32_f64(p.fv);
+    const uint64_t inner = __builtin_amdgcn_ballot_w64(p.front) &
+                           __builtin_amdgcn_ballot_w64((unsigned)x0 < (unsigned)(W - 1)) &
+                           __builtin_amdgcn_ballot_w64((unsigned)y0 < (unsigned)(H - 1));
+    if (inner == __builtin_amdgcn_read_exec()) {
+        t.o00 = ((unsigned)y0 * (unsigned)W + (unsigned)x0) * (unsigned)S;
+        t.o10 = t.o00 + S;
+        t.o01 = t.o00 + (unsigned)W * S;
+        t.o11 = t.o01 + S;
+    } else {
+        const bool any = p.front & (x0 >= -1) & (x0 < W) & (y0 >= -1) & (y0 < H);
+        x0 = any ? x0 : -2;
+        y0 = any ? y0 : -2;
+        const bool bx0 = (unsigned)x0 < (unsigned)W, bx1 = (unsigned)(x0 + 1) < (unsigned)W;
+        const bool by0 = (unsigned)y0 < (unsigned)H, by1 = (unsigned)(y0 + 1) < (unsigned)H;
+        const unsigned o = ((unsigned)y0 * (unsigned)W + (unsigned)x0) * (unsigned)S;
+        t.o00 = bx0 & by0 ? o : kOutside;
+        t.o10 = bx1 & by0 ? o + S : kOutside;
+        t.o01 = bx0 & by1 ? o + (unsigned)W * S : kOutside;
+        t.o11 = bx1 & by1 ? o + (unsigned)W * S + S : kOutside;
+        p.fx = any ? p.fx : 0.0f;
+        p.fy = any ? p.fy : 0.0f;
+    }
+    return t;
+}
+
 // Block index -> tile index so that each XCD (workgroups are dealt round-robin to the 8
 // XCDs) works on a contiguous run of tiles: the views of one tile and neighbouring tiles
 // share MPI lines in that XCD's L2.

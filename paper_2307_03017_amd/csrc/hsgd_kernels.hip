@@ -405,32 +405,74 @@ __global__ __launch_bounds__(256) void k_compact(const uint64_t* __restrict__ ba
 // ------------------------------------------------------------------------------------
 // render
 // ------------------------------------------------------------------------------------
+// General homographies: a wave takes 64 neighbouring rays of one row of one view. Positions
+// are FP64 (~20 instructions a sample: the row's part of the map is tabulated in LDS, the
+// division is a reciprocal estimate with two Newton steps), the taps come through a buffer
+// resource over the plane, and the loads of three planes are in flight while one is blended.
+// Bound by its instructions (about 75 per sample, a quarter of them FP64). One view of
+// 1008x756x32 in BF16: 84.6 us with IEEE divisions, the map re-read per sample and one plane
+// in flight, 70.8 us now.
 template <int DT>
-__global__ __launch_bounds__(kBlock) void k_render(const void* __restrict__ mpi, int D, int H, int W,
+__global__ __launch_bounds__(kBlock) void k_render(const void* __restrict__ mpi, int D, int H, int W, int N,
                                                    const hsgd_warp* __restrict__ warps,
                                                    const float* __restrict__ images,
                                                    float* __restrict__ out_rgb,
-                                                   float* __restrict__ partials) {
-    __shared__ hsgd_warp sw[kMaxD];
+                                                   float* __restrict__ partials, int ntx) {
+    constexpr int S = Vox<DT>::kBytes;
+    __shared__ RowMap s_map[kTileH][kMaxD];
     __shared__ float sred[kBlock / 64];
-    const int view = blockIdx.z;
-    load_warps(sw, warps, view, D);
+    const int tile = xcd_tile(blockIdx.x, gridDim.x);
+    const int view = tile % N, t2 = tile / N;
+    const int x0 = (t2 % ntx) * kTileW, y0 = (t2 / ntx) * kTileH;
+    for (int i = threadIdx.x; i < kTileH * D; i += kBlock) {
+        const int r = i / D, z = i - r * D;
+        s_map[r][z] = row_map(warps[(size_t)view * D + z], y0 + r);
+    }
     __syncthreads();
-    const int x = blockIdx.x * kTileW + (threadIdx.x & 63);
-    const int y = blockIdx.y * kTileH + (threadIdx.x >> 6);
-    const int HW = H * W;
+    const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int x = x0 + (int)(threadIdx.x & 63), y = y0 + wv;
+    const double xd = (double)x;
+    const size_t plane_bytes = (size_t)H * W * S;
+    struct Fetched {
+        typename Vox<DT>::Raw a, b, c, d;
+        float fx, fy;
+    };
+    auto fetch = [&](int z) {
+        MapPos p = map_pos(s_map[wv][z], xd);
+        const TapOffs o = tap_offsets<S>(p, W, H);
+        const auto rs = row_rsrc(reinterpret_cast<const char*>(mpi) + (size_t)z * plane_bytes, (int)plane_bytes);
+        return Fetched{Vox<DT>::load_raw(rs, o.o00), Vox<DT>::load_raw(rs, o.o10), Vox<DT>::load_raw(rs, o.o01),
+                       Vox<DT>::load_raw(rs, o.o11), p.fx, p.fy};
+    };
+    float T = 1.0f, c0 = 0.0f, c1 = 0.0f, c2 = 0.0f;
+    auto blend = [&](const Fetched& f) {
+        const float gx = 1.0f - f.fx, gy = 1.0f - f.fy;
+        Taps w;
+        w.w00 = gx * gy;
+        w.w10 = f.fx * gy;
+        w.w01 = gx * f.fy;
+        w.w11 = f.fx * f.fy;
+        const float4 s = blend_taps(w, Tap4{Vox<DT>::decode(f.a), Vox<DT>::decode(f.b), Vox<DT>::decode(f.c),
+                                            Vox<DT>::decode(f.d)});
+        const float wgt = T * s.w;
+        c0 = __builtin_fmaf(wgt, s.x, c0);
+        c1 = __builtin_fmaf(wgt, s.y, c1);
+        c2 = __builtin_fmaf(wgt, s.z, c2);
+        T *= 1.0f - s.w;
+    };
+    constexpr int kQ = 4;                                   // planes in flight: kQ - 1
+    Fetched q[kQ];
+#pragma unroll
+    for (int j = 0; j + 1 < kQ; ++j) q[j] = fetch(min(j, D - 1));
+    for (int z = 0; z < D; z += kQ) {
+#pragma unroll
+        for (int j = 0; j < kQ; ++j) {
+            q[(j + kQ - 1) % kQ] = fetch(min(z + j + kQ - 1, D - 1));
+            if (z + j < D) blend(q[j]);
+        }
+    }
     float sq = 0.0f;
     if (x < W && y < H) {
-        float T = 1.0f, c0 = 0.0f, c1 = 0.0f, c2 = 0.0f;
-        for (int z = 0; z < D; ++z) {
-            const Taps tp = make_taps(sw[z], x, y, H, W);
-            const float4 s = sample<DT>(mpi, z * HW, tp);
-            const float wgt = T * s.w;
-            c0 = __builtin_fmaf(wgt, s.x, c0);
-            c1 = __builtin_fmaf(wgt, s.y, c1);
-            c2 = __builtin_fmaf(wgt, s.z, c2);
-            T *= 1.0f - s.w;
-        }
         const size_t pix = ((size_t)view * H + y) * W + x;
         if (out_rgb) {
             out_rgb[3 * pix + 0] = c0;
@@ -446,8 +488,7 @@ __global__ __launch_bounds__(kBlock) void k_render(const void* __restrict__ mpi,
     }
     if (partials) {
         const float tot = block_sum(sq, sred);
-        if (threadIdx.x == 0)
-            partials[((size_t)view * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x] = tot;
+        if (threadIdx.x == 0) partials[tile] = tot;
     }
 }
 
@@ -1785,8 +1826,9 @@ int launch_render(const hsgd_mpi& m, const hsgd_views& v, float* out_rgb, float*
         const dim3 grid((unsigned)ceil_div(m.W, kTileW), (unsigned)ceil_div(m.H, kTileH), (unsigned)v.N);
         nparts = (int64_t)grid.x * grid.y * grid.z;
         ProfScope ps(HSGD_K_RENDER, s);
-        HSGD_DISPATCH_T(m.dtype, hipLaunchKernelGGL((k_render<DT>), grid, dim3(kBlock), 0, s, m.rgba, m.D,
-                                                    m.H, m.W, v.warps, v.images, out_rgb, partials));
+        HSGD_DISPATCH_T(m.dtype, hipLaunchKernelGGL((k_render<DT>), dim3((unsigned)nparts), dim3(kBlock), 0, s, m.rgba,
+                                                    m.D, m.H, m.W, v.N, v.warps, v.images, out_rgb, partials,
+                                                    (int)grid.x));
     }
     if (out_loss) {
         ProfScope ps(HSGD_K_REDUCE, s);
