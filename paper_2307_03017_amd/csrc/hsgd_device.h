@@ -8,13 +8,18 @@
 namespace hsgd {
 namespace {
 
-// FP32 -> BF16 bits, round to nearest even (NaN stays a quiet NaN).
-__device__ __forceinline__ uint32_t f32_to_bf16_bits(float f) {
-    uint32_t u = __float_as_uint(f);
-    if ((u & 0x7fffffffu) > 0x7f800000u) return (u >> 16) | 0x40u;  // quiet NaN
-    u += 0x7fffu + ((u >> 16) & 1u);
-    return u >> 16;
+// Two FP32 values -> BF16 bits (a in the low half), round to nearest even, a NaN kept as a
+// quiet NaN: one v_cvt_pk_bf16_f32, checked over every FP32 bit pattern against the integer
+// form (add 0x7fff and the bit above, shift, NaNs apart), whose compare and branch per value
+// were a third of the instructions of a BF16 plane sweep (1008x756x32, 5 tilted views: 419 us
+// a call with it, 367 us without; the finest level transition of a 1920x1080x64 refine: 437
+// and 353 us).
+__device__ __forceinline__ uint32_t f32x2_to_bf16x2(float a, float b) {
+    typedef float f32x2 __attribute__((ext_vector_type(2)));
+    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2{a, b}), bf16x2));
 }
+__device__ __forceinline__ uint32_t f32_to_bf16_bits(float f) { return f32x2_to_bf16x2(f, 0.0f); }
 
 // Raw (untyped, stride 0) buffer resource over one MPI row of n_bytes bytes: loads at
 // offsets outside [0, n_bytes) return 0, which is the zero padding of a plane outside the

@@ -76,19 +76,12 @@ struct Vox<HSGD_BF16> {
         return __uint_as_float((uint32_t)reinterpret_cast<const uint16_t*>(base)[4 * (size_t)i + 3] << 16);
     }
     static __device__ __forceinline__ void store(void* base, int i, float4 v) {
-        uint2 r;
-        r.x = f32_to_bf16_bits(v.x) | (f32_to_bf16_bits(v.y) << 16);
-        r.y = f32_to_bf16_bits(v.z) | (f32_to_bf16_bits(v.w) << 16);
-        reinterpret_cast<uint2*>(base)[i] = r;
+        reinterpret_cast<uint2*>(base)[i] = make_uint2(f32x2_to_bf16x2(v.x, v.y), f32x2_to_bf16x2(v.z, v.w));
     }
     // voxels i and i + 1 (i even: one 16-byte store)
     static __device__ __forceinline__ void store2(void* base, int i, float4 a, float4 b) {
-        uint4 r;
-        r.x = f32_to_bf16_bits(a.x) | (f32_to_bf16_bits(a.y) << 16);
-        r.y = f32_to_bf16_bits(a.z) | (f32_to_bf16_bits(a.w) << 16);
-        r.z = f32_to_bf16_bits(b.x) | (f32_to_bf16_bits(b.y) << 16);
-        r.w = f32_to_bf16_bits(b.z) | (f32_to_bf16_bits(b.w) << 16);
-        reinterpret_cast<uint4*>(base)[i >> 1] = r;
+        reinterpret_cast<uint4*>(base)[i >> 1] = make_uint4(f32x2_to_bf16x2(a.x, a.y), f32x2_to_bf16x2(a.z, a.w),
+                                                            f32x2_to_bf16x2(b.x, b.y), f32x2_to_bf16x2(b.z, b.w));
     }
     static __device__ __forceinline__ float4 load_row(const char* row, unsigned col) {
         const uint2 r = *reinterpret_cast<const uint2*>(row + (col << 3));
@@ -115,8 +108,7 @@ struct Vox<HSGD_BF16> {
     }
     // the value a store followed by a load returns (round to nearest even, NaN quieted)
     static __device__ __forceinline__ float4 stored(float4 v) {
-        return make_float4(__uint_as_float(f32_to_bf16_bits(v.x) << 16), __uint_as_float(f32_to_bf16_bits(v.y) << 16),
-                           __uint_as_float(f32_to_bf16_bits(v.z) << 16), __uint_as_float(f32_to_bf16_bits(v.w) << 16));
+        return decode(make_uint2(f32x2_to_bf16x2(v.x, v.y), f32x2_to_bf16x2(v.z, v.w)));
     }
 };
 

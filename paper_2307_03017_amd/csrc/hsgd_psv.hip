@@ -59,10 +59,8 @@ __device__ __forceinline__ void psv_store_tile(const float* __restrict__ s, int 
             if ((TH * RQ % 256 == 0 || e < TH * RQ) && r < vh && c < vq) {
                 const float4 a = reinterpret_cast<const float4*>(s)[2 * e];
                 const float4 b = reinterpret_cast<const float4*>(s)[2 * e + 1];
-                const u32x4 q{f32_to_bf16_bits(a.x) | (f32_to_bf16_bits(a.y) << 16),
-                              f32_to_bf16_bits(a.z) | (f32_to_bf16_bits(a.w) << 16),
-                              f32_to_bf16_bits(b.x) | (f32_to_bf16_bits(b.y) << 16),
-                              f32_to_bf16_bits(b.z) | (f32_to_bf16_bits(b.w) << 16)};
+                const u32x4 q{f32x2_to_bf16x2(a.x, a.y), f32x2_to_bf16x2(a.z, a.w), f32x2_to_bf16x2(b.x, b.y),
+                              f32x2_to_bf16x2(b.z, b.w)};
                 st_stream(q, reinterpret_cast<u32x4*>(o + (size_t)r * Wl * 3) + c);
             }
         }
