@@ -31,63 +31,6 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t row_rsrc(const char* row, int 
 }
 
 // ------------------------------------------------------------------------------------
-// bilinear taps of one (view pixel, plane): zero padding, pixel-index coordinates
-// ------------------------------------------------------------------------------------
-struct Taps {
-    int i00, i10, i01, i11;        // flat pixel index y*W + x (clamped; weight 0 if outside)
-    float w00, w10, w01, w11;
-};
-
-__device__ __forceinline__ Taps make_taps(const hsgd_warp& wp, int x, int y, int H, int W) {
-    int x0, y0;
-    float fx, fy;
-    bool front = true;
-    if (wp.is_shift) {
-        x0 = x + wp.ix;
-        y0 = y + wp.iy;
-        fx = wp.fx;
-        fy = wp.fy;
-    } else {
-        // The position in FP64 from the FP64 map: its error (~1e-12 px) is far below the
-        // FP32 rounding of the fractions, so the taps and weights are those of the exact
-        // position, as for a translation.
-        const double xd = (double)x, yd = (double)y;
-        const double q0 = __builtin_fma(wp.G[0], xd, __builtin_fma(wp.G[1], yd, wp.G[2]));
-        const double q1 = __builtin_fma(wp.G[3], xd, __builtin_fma(wp.G[4], yd, wp.G[5]));
-        const double q2 = __builtin_fma(wp.G[6], xd, __builtin_fma(wp.G[7], yd, wp.G[8]));
-        front = q2 > 0.0;
-        double u = -8.0, v = -8.0;
-        if (front) {
-            const double r = 1.0 / q2;
-            u = q0 * r;
-            v = q1 * r;
-        }
-        u = fmin(fmax(u, -8.0), (double)W + 8.0);   // NaN -> -8 (outside)
-        v = fmin(fmax(v, -8.0), (double)H + 8.0);
-        const double fu = floor(u), fv = floor(v);
-        x0 = (int)fu;
-        y0 = (int)fv;
-        fx = (float)(u - fu);
-        fy = (float)(v - fv);
-    }
-    const bool bx0 = (unsigned)x0 < (unsigned)W, bx1 = (unsigned)(x0 + 1) < (unsigned)W;
-    const bool by0 = (unsigned)y0 < (unsigned)H, by1 = (unsigned)(y0 + 1) < (unsigned)H;
-    const int cx0 = min(max(x0, 0), W - 1), cx1 = min(max(x0 + 1, 0), W - 1);
-    const int cy0 = min(max(y0, 0), H - 1), cy1 = min(max(y0 + 1, 0), H - 1);
-    Taps t;
-    t.i00 = cy0 * W + cx0;
-    t.i10 = cy0 * W + cx1;
-    t.i01 = cy1 * W + cx0;
-    t.i11 = cy1 * W + cx1;
-    const float gx = 1.0f - fx, gy = 1.0f - fy;
-    t.w00 = (front && bx0 && by0) ? gx * gy : 0.0f;
-    t.w10 = (front && bx1 && by0) ? fx * gy : 0.0f;
-    t.w01 = (front && bx0 && by1) ? gx * fy : 0.0f;
-    t.w11 = (front && bx1 && by1) ? fx * fy : 0.0f;
-    return t;
-}
-
-// ------------------------------------------------------------------------------------
 // positions under a general homography, one row of pixels at a time
 // ------------------------------------------------------------------------------------
 // The homogeneous position of pixel x of a fixed row y: q_i = a_i x + b_i, the products of y
@@ -146,15 +89,23 @@ __device__ __forceinline__ int cvt_i32_f64(double d) {
     asm("v_cvt_i32_f64 %0, %1" : "=v"(i) : "v"(d));
     return i;
 }
+// For a kernel that also scatters: the top-left tap's cell y0 W + x0 and which of the two tap
+// columns (bits 0, 1) and rows (bits 2, 3) lie in the plane.
+struct TapCell {
+    int cell;
+    unsigned in;
+};
 template <int S>
-__device__ __forceinline__ TapOffs tap_offsets(MapPos& p, int W, int H) {
+__device__ __forceinline__ TapOffs tap_offsets(MapPos& p, int W, int H, TapCell& c) {
     TapOffs t;
     int x0 = cvt_i32_f64(p.fu), y0 = cvt_i32_f64(p.fv);
     const uint64_t inner = __builtin_amdgcn_ballot_w64(p.front) &
                            __builtin_amdgcn_ballot_w64((unsigned)x0 < (unsigned)(W - 1)) &
                            __builtin_amdgcn_ballot_w64((unsigned)y0 < (unsigned)(H - 1));
     if (inner == __builtin_amdgcn_read_exec()) {
-        t.o00 = ((unsigned)y0 * (unsigned)W + (unsigned)x0) * (unsigned)S;
+        c.cell = y0 * W + x0;
+        c.in = 15u;
+        t.o00 = (unsigned)c.cell * (unsigned)S;
         t.o10 = t.o00 + S;
         t.o01 = t.o00 + (unsigned)W * S;
         t.o11 = t.o01 + S;
@@ -164,15 +115,22 @@ __device__ __forceinline__ TapOffs tap_offsets(MapPos& p, int W, int H) {
         y0 = any ? y0 : -2;
         const bool bx0 = (unsigned)x0 < (unsigned)W, bx1 = (unsigned)(x0 + 1) < (unsigned)W;
         const bool by0 = (unsigned)y0 < (unsigned)H, by1 = (unsigned)(y0 + 1) < (unsigned)H;
-        const unsigned o = ((unsigned)y0 * (unsigned)W + (unsigned)x0) * (unsigned)S;
-        t.o00 = bx0 & by0 ? o : kOutside;
-        t.o10 = bx1 & by0 ? o + S : kOutside;
-        t.o01 = bx0 & by1 ? o + (unsigned)W * S : kOutside;
-        t.o11 = bx1 & by1 ? o + (unsigned)W * S + S : kOutside;
+        c.cell = y0 * W + x0;
+        c.in = (bx0 ? 1u : 0u) | (bx1 ? 2u : 0u) | (by0 ? 4u : 0u) | (by1 ? 8u : 0u);
+        const unsigned o = (unsigned)c.cell * (unsigned)S;
+        t.o00 = bx0 && by0 ? o : kOutside;
+        t.o10 = bx1 && by0 ? o + S : kOutside;
+        t.o01 = bx0 && by1 ? o + (unsigned)W * S : kOutside;
+        t.o11 = bx1 && by1 ? o + (unsigned)W * S + S : kOutside;
         p.fx = any ? p.fx : 0.0f;
         p.fy = any ? p.fy : 0.0f;
     }
     return t;
+}
+template <int S>
+__device__ __forceinline__ TapOffs tap_offsets(MapPos& p, int W, int H) {
+    TapCell c;
+    return tap_offsets<S>(p, W, H, c);
 }
 
 // Block index -> tile index so that each XCD (workgroups are dealt round-robin to the 8

@@ -16,6 +16,8 @@
 //               computes up to three such levels from one read of the finer images
 #include <hip/hip_runtime.h>
 
+#include <climits>
+
 #include "hsgd_device.h"
 #include "hsgd_internal.h"
 
@@ -112,26 +114,32 @@ struct Vox<HSGD_BF16> {
     }
 };
 
-// The four taps of a sample, loaded, and their bilinear blend (explicit FMAs: every scan
-// that samples a plane gets the same bits).
+// A sample of a general map: the four taps as stored and their bilinear blend (explicit FMAs:
+// every scan that samples a plane gets the same bits).
+template <int DT>
 struct Tap4 {
-    float4 a, b, c, d;
+    typename Vox<DT>::Raw a, b, c, d;
 };
 template <int DT>
-__device__ __forceinline__ Tap4 load_taps(const void* mpi, int plane_base, const Taps& t) {
-    return Tap4{Vox<DT>::load(mpi, plane_base + t.i00), Vox<DT>::load(mpi, plane_base + t.i10),
-                Vox<DT>::load(mpi, plane_base + t.i01), Vox<DT>::load(mpi, plane_base + t.i11)};
+__device__ __forceinline__ Tap4<DT> load_taps(__amdgpu_buffer_rsrc_t plane, const TapOffs& o) {
+    return Tap4<DT>{Vox<DT>::load_raw(plane, o.o00), Vox<DT>::load_raw(plane, o.o10), Vox<DT>::load_raw(plane, o.o01),
+                    Vox<DT>::load_raw(plane, o.o11)};
 }
-__device__ __forceinline__ float4 blend_taps(const Taps& t, const Tap4& v) {
+struct TapW {
+    float w00, w10, w01, w11;
+};
+__device__ __forceinline__ TapW tap_weights(float fx, float fy) {
+    const float gx = 1.0f - fx, gy = 1.0f - fy;
+    return TapW{gx * gy, fx * gy, gx * fy, fx * fy};
+}
+template <int DT>
+__device__ __forceinline__ float4 blend_taps(const TapW& t, const Tap4<DT>& r) {
+    const float4 va = Vox<DT>::decode(r.a), vb = Vox<DT>::decode(r.b), vc = Vox<DT>::decode(r.c), vd = Vox<DT>::decode(r.d);
     auto f = [&](float a, float b, float c, float d) {
         return __builtin_fmaf(t.w11, d, __builtin_fmaf(t.w01, c, __builtin_fmaf(t.w10, b, t.w00 * a)));
     };
-    return make_float4(f(v.a.x, v.b.x, v.c.x, v.d.x), f(v.a.y, v.b.y, v.c.y, v.d.y), f(v.a.z, v.b.z, v.c.z, v.d.z),
-                       f(v.a.w, v.b.w, v.c.w, v.d.w));
-}
-template <int DT>
-__device__ __forceinline__ float4 sample(const void* mpi, int plane_base, const Taps& t) {
-    return blend_taps(t, load_taps<DT>(mpi, plane_base, t));
+    return make_float4(f(va.x, vb.x, vc.x, vd.x), f(va.y, vb.y, vc.y, vd.y), f(va.z, vb.z, vc.z, vd.z),
+                       f(va.w, vb.w, vc.w, vd.w));
 }
 
 __device__ __forceinline__ float wave_sum(float v) {
@@ -149,13 +157,6 @@ __device__ __forceinline__ float block_sum(float v, float* sh) {
     if (threadIdx.x == 0)
         for (int i = 0; i < (int)(blockDim.x >> 6); ++i) r += sh[i];
     return r;
-}
-
-__device__ __forceinline__ void load_warps(hsgd_warp* sw, const hsgd_warp* warps, int view, int D) {
-    constexpr int kWords = (int)(sizeof(hsgd_warp) / sizeof(int));
-    const int* src = reinterpret_cast<const int*>(warps + (size_t)view * D);
-    int* dst = reinterpret_cast<int*>(sw);
-    for (int i = threadIdx.x; i < D * kWords; i += blockDim.x) dst[i] = src[i];
 }
 
 // ------------------------------------------------------------------------------------
@@ -426,26 +427,18 @@ __global__ __launch_bounds__(kBlock) void k_render(const void* __restrict__ mpi,
     const double xd = (double)x;
     const size_t plane_bytes = (size_t)H * W * S;
     struct Fetched {
-        typename Vox<DT>::Raw a, b, c, d;
+        Tap4<DT> t;
         float fx, fy;
     };
     auto fetch = [&](int z) {
         MapPos p = map_pos(s_map[wv][z], xd);
         const TapOffs o = tap_offsets<S>(p, W, H);
         const auto rs = row_rsrc(reinterpret_cast<const char*>(mpi) + (size_t)z * plane_bytes, (int)plane_bytes);
-        return Fetched{Vox<DT>::load_raw(rs, o.o00), Vox<DT>::load_raw(rs, o.o10), Vox<DT>::load_raw(rs, o.o01),
-                       Vox<DT>::load_raw(rs, o.o11), p.fx, p.fy};
+        return Fetched{load_taps<DT>(rs, o), p.fx, p.fy};
     };
     float T = 1.0f, c0 = 0.0f, c1 = 0.0f, c2 = 0.0f;
     auto blend = [&](const Fetched& f) {
-        const float gx = 1.0f - f.fx, gy = 1.0f - f.fy;
-        Taps w;
-        w.w00 = gx * gy;
-        w.w10 = f.fx * gy;
-        w.w01 = gx * f.fy;
-        w.w11 = f.fx * f.fy;
-        const float4 s = blend_taps(w, Tap4{Vox<DT>::decode(f.a), Vox<DT>::decode(f.b), Vox<DT>::decode(f.c),
-                                            Vox<DT>::decode(f.d)});
+        const float4 s = blend_taps<DT>(tap_weights(f.fx, f.fy), f.t);
         const float wgt = T * s.w;
         c0 = __builtin_fmaf(wgt, s.x, c0);
         c1 = __builtin_fmaf(wgt, s.y, c1);
@@ -515,10 +508,31 @@ __device__ __forceinline__ int slot_rank(uint64_t m, int z, int kcap) {
 }
 
 // ------------------------------------------------------------------------------------
-// gradient, general warps: per-ray scans, atomic transposed-bilinear scatter
+// gradient, general warps: per-ray scans, transposed-bilinear scatter with atomics
+//
+// A workgroup takes 64 x 8 rays of one view; lane 63 of each wave only receives what lane 62
+// sends to its right (its ray belongs to the next tile). Both scans are rolled loops over
+// pairs of planes, so any plane count runs its own planes only (an odd count one transparent
+// plane more). The front-to-back scan leaves the transmittance in front of each pair in LDS;
+// the back-to-front scan samples a pair again and recomputes the second transmittance with
+// the same operation.
+//
+// Scatter. A ray touches four cells of a plane; neighbouring rays nearly always share them.
+// The right column of lane i - 1 is added to the left column of lane i, and the lower row of
+// a wave to the upper row of the next wave through LDS, where the cells are the same, so
+// about 1.15 cells per ray remain. Those that are selected are staged in LDS, and 64 at a
+// time added to the slots with four lanes per cell: the memory system takes about 22 G
+// 64-byte atomic requests a second whatever they hold, and a float4 added by one lane is
+// four requests instead of one. A wave none of whose cells is selected (about half of them
+// with 4 of 32 planes kept) skips a plane's adjoint and scatter.
+// Bound by the two scans, FP64 positions and four tap loads a sample at 4 waves per SIMD, and
+// in a dense gradient by the atomics. 512x384x32, 4 tilted views, k = 4: 672 us with an IEEE
+// division per position and one atomic per lane and channel, 289 us now; the dense gradient
+// of 501x333x24, 2 tilted views: 693 and 198 us. Taps of the next pair in flight behind the
+// scatter, at 3 waves per SIMD or with spills at 4, measured slower (311 and 399 us), and so
+// did 4 rows per workgroup in the dense gradient (207 us).
 // ------------------------------------------------------------------------------------
-// Whole-wave lane shifts for the general-warp scatter: lane i <- lane i-1 / lane i+1; a lane
-// without a source gets `none`.
+// Whole-wave lane shifts: lane i <- lane i-1 / lane i+1; a lane without a source gets `none`.
 __device__ __forceinline__ int lane_prev_i(int v, int none) {
     return __builtin_amdgcn_update_dpp(none, v, 0x138, 0xF, 0xF, false);
 }
@@ -529,62 +543,168 @@ __device__ __forceinline__ float4 lane_prev_f4(float4 v) {
     auto f = [](float a) { return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(a), 0x138, 0xF, 0xF, false)); };
     return make_float4(f(v.x), f(v.y), f(v.z), f(v.w));
 }
-
-// One tap's contribution to the slots: cell c (-1: none) of plane z, value g.
-__device__ __forceinline__ void scatter_cell(float4* __restrict__ slots, const uint64_t* __restrict__ mask,
-                                             uint64_t full, int kcap, int HW, int z, int c, const float4& g) {
-    if (c < 0) return;
-    const int r = slot_rank(mask ? mask[c] : full, z, kcap);
-    if (r < 0) return;
-    float* dst = reinterpret_cast<float*>(slots + (size_t)r * HW + c);
-    atomicAdd(dst + 0, g.x);
-    atomicAdd(dst + 1, g.y);
-    atomicAdd(dst + 2, g.z);
-    atomicAdd(dst + 3, g.w);
+__device__ __forceinline__ float4 only_if(bool c, const float4& a) {
+    return make_float4(c ? a.x : 0.0f, c ? a.y : 0.0f, c ? a.z : 0.0f, c ? a.w : 0.0f);
+}
+__device__ __forceinline__ float4 add4(const float4& a, const float4& b) {
+    return make_float4(a.x + b.x, a.y + b.y, a.z + b.z, a.w + b.w);
+}
+__device__ __forceinline__ float4 scale4(float w, const float4& g) {
+    return make_float4(w * g.x, w * g.y, w * g.z, w * g.w);
 }
 
+// slot_rank for a plane that differs by lane, in 32-bit steps. (A 64-bit shift by a VGPR that
+// is the last of the kernel's allocation gave wrong bits now and then: with 128 registers and
+// the amount in v127, entries of the ring below were dropped.)
+__device__ __forceinline__ int slot_rank_lane(uint64_t m, unsigned z, int kcap) {
+    const unsigned lo = (unsigned)m, hi = (unsigned)(m >> 32);
+    const bool far = z >= 32u;
+    const unsigned w = far ? hi : lo, b = 1u << (z & 31u);
+    const int r = __popc(w & (b - 1u)) + (far ? __popc(lo) : 0);
+    return (w & b) != 0u && r < kcap ? r : -1;
+}
+
+// What one lane wrote to LDS before this another lane of the wave reads after it (the LDS
+// operations of a wave execute in order; this keeps the compiler from moving them).
+__device__ __forceinline__ void wave_lds_fence() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    asm volatile("" ::: "memory");
+}
+
+// One wave's cells on their way to the slots: a ring of values and the cells they go to
+// (cell | plane << 26: H W <= 2^26 and z < 64), emptied 64 at a time. Emptying reads a mask
+// word per lane to find each cell's slot, so that a stray cell, whose word nobody loaded
+// ahead, costs a 64th of a memory latency; then four lanes add one cell.
+constexpr int kStage = 128;
+struct GradStage {
+    float4 v[kStage];
+    unsigned to[kStage];
+};
+struct GradSink {
+    GradStage* st;
+    float4* slots;
+    const uint64_t* mask;
+    uint64_t full;
+    int lane, HW, kcap;
+    int head, count;                     // wave-uniform
+    __device__ void flush(int n) {
+        wave_lds_fence();
+        if (lane < n) {
+            const int i = (head + lane) & (kStage - 1);
+            const unsigned to = st->to[i], cell = to & ((1u << 26) - 1);
+            const int r = slot_rank_lane(mask ? mask[cell] : full, to >> 26, kcap);
+            st->to[i] = r >= 0 ? (unsigned)r * (unsigned)HW + cell : ~0u;
+        }
+        wave_lds_fence();
+        for (int e0 = 0; e0 < n; e0 += 16) {
+            const int e = e0 + (lane >> 2);
+            const int i = (head + e) & (kStage - 1);
+            const unsigned slot = e < n ? st->to[i] : ~0u;
+            if (slot != ~0u)
+                atomicAdd(reinterpret_cast<float*>(reinterpret_cast<char*>(slots) + (slot * 16u + (lane & 3) * 4u)),
+                          reinterpret_cast<const float*>(st->v)[4 * i + (lane & 3)]);
+        }
+        head = (head + n) & (kStage - 1);
+        count -= n;
+        wave_lds_fence();
+    }
+    // lanes with `on` add v to the cell of plane z (every lane of the wave calls it)
+    __device__ void put(bool on, int z, int cell, const float4& v) {
+        const uint64_t b = __builtin_amdgcn_ballot_w64(on);
+        if (b == 0) return;
+        const int r = (int)__builtin_amdgcn_mbcnt_hi((unsigned)(b >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)b, 0u));
+        const int i = (head + count + r) & (kStage - 1);
+        if (on) {
+            st->v[i] = v;
+            st->to[i] = (unsigned)cell | ((unsigned)z << 26);
+        }
+        count += __popcll(b);
+        if (count >= 64) flush(64);
+    }
+};
+
+constexpr int kGenOX = 63, kGenY = 8;
+constexpr int kGenThreads = 64 * kGenY;
 template <int DT, int MAXD>
-__global__ __launch_bounds__(kBlock) void k_grad(const void* __restrict__ mpi, int D, int H, int W,
-                                                 const hsgd_warp* __restrict__ warps,
-                                                 const float* __restrict__ images,
-                                                 const float* __restrict__ dimg,
-                                                 const uint64_t* __restrict__ mask, int kcap,
-                                                 float inv_n, float4* __restrict__ slots,
-                                                 float* __restrict__ partials) {
-    __shared__ hsgd_warp sw[MAXD];
-    __shared__ float sred[kBlock / 64];
-    // per plane parity: every lane's left-column tap cells (top, bottom) and its bottom-left
-    // contribution, for the row merge between neighbouring waves
-    __shared__ int s_cell[2][2][kBlock];
-    __shared__ float4 s_low[2][kBlock];
-    const int view = blockIdx.z;
-    load_warps(sw, warps, view, D);
-    __syncthreads();
-    const int x = blockIdx.x * kTileW + (threadIdx.x & 63);
-    const int y = blockIdx.y * kTileH + (threadIdx.x >> 6);
-    const int HW = H * W;
-    const uint64_t full = plane_bits(D);
-    // every lane runs both scans (a lane past the frame samples clamped taps and carries a
-    // zero residual), so that neighbouring lanes can merge their shared taps below
-    const bool ray = x < W && y < H;
-    float sq = 0.0f;
-    float Ts[MAXD];
-    float T = 1.0f, c0 = 0.0f, c1 = 0.0f, c2 = 0.0f;
-#pragma unroll
-    for (int z = 0; z < MAXD; ++z) {
+__global__ __launch_bounds__(kGenThreads) __attribute__((amdgpu_waves_per_eu(4))) void k_grad(
+    const void* __restrict__ mpi, int D, int H, int W, int N, const hsgd_warp* __restrict__ warps,
+    const float* __restrict__ images, const float* __restrict__ dimg, const uint64_t* __restrict__ mask, int kcap,
+    float inv_n, float4* __restrict__ slots, float* __restrict__ partials, int ntx) {
+    constexpr int S = Vox<DT>::kBytes;
+    __shared__ double s_map[MAXD][10];                      // G of each plane (rows of three, padded)
+    __shared__ float s_T[MAXD / 2][kGenThreads];            // transmittance in front of each pair of planes
+    // by plane parity: every lane's left-column cell and what it holds for the row below
+    __shared__ int s_key[2][kGenThreads];
+    __shared__ float4 s_low[2][kGenThreads];
+    __shared__ GradStage s_stage[kGenY];
+    __shared__ float sred[kGenY];
+    const int tile = xcd_tile(blockIdx.x, gridDim.x);
+    const int view = tile % N, t2 = tile / N;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int x = (t2 % ntx) * kGenOX + lane, y = (t2 / ntx) * kGenY + wv;
+    const int HW = H * W, D2 = (D + 1) & ~1;
+    for (int z = tid; z < D2; z += kGenThreads) {
+        double g[9] = {0, 0, 0, 0, 0, 0, 0, 0, -1.0};       // planes behind the last: nowhere in front
         if (z < D) {
-            const Taps tp = make_taps(sw[z], x, y, H, W);
-            const float4 s = sample<DT>(mpi, z * HW, tp);
-            Ts[z] = T;
-            const float wgt = T * s.w;
-            c0 = __builtin_fmaf(wgt, s.x, c0);
-            c1 = __builtin_fmaf(wgt, s.y, c1);
-            c2 = __builtin_fmaf(wgt, s.z, c2);
-            T *= 1.0f - s.w;
+            const hsgd_warp& w = warps[(size_t)view * D + z];
+            const RowMap m0 = row_map(w, 0);
+            g[0] = m0.a0;
+            g[1] = w.is_shift ? 0.0 : w.G[1];
+            g[2] = m0.b0;
+            g[3] = m0.a1;
+            g[4] = w.is_shift ? 1.0 : w.G[4];
+            g[5] = m0.b1;
+            g[6] = m0.a2;
+            g[7] = w.is_shift ? 0.0 : w.G[7];
+            g[8] = m0.b2;
+        }
+        for (int i = 0; i < 9; ++i) s_map[z][i] = g[i];
+    }
+    __syncthreads();
+    // rays that contribute; the other lanes sample like the rest and carry a zero residual
+    const bool own = lane < kGenOX && x < W && y < H;
+    const double xd = (double)x, yd = (double)y;
+    const size_t plane_bytes = (size_t)HW * S;
+    struct Fetched {
+        Tap4<DT> t;
+        float fx, fy;
+    };
+    auto fetch = [&](int z, TapOffs& o, TapCell& c) {
+        const double* g = s_map[z];
+        MapPos p = map_pos(RowMap{g[0], g[3], g[6], __builtin_fma(g[1], yd, g[2]), __builtin_fma(g[4], yd, g[5]),
+                                  __builtin_fma(g[7], yd, g[8])}, xd);
+        o = tap_offsets<S>(p, W, H, c);
+        return Fetched{load_taps<DT>(row_rsrc(reinterpret_cast<const char*>(mpi) + (size_t)min(z, D - 1) * plane_bytes,
+                                              (int)plane_bytes), o), p.fx, p.fy};
+    };
+    float T = 1.0f, c0 = 0.0f, c1 = 0.0f, c2 = 0.0f;
+    {
+        constexpr int kA = DT == HSGD_BF16 ? 3 : 2;         // planes in flight behind the current one
+        Fetched q[4];
+        TapOffs o;
+        TapCell c;
+#pragma unroll
+        for (int j = 0; j < kA; ++j) q[j] = fetch(min(j, D2 - 1), o, c);
+        for (int z = 0; z < D2; z += 4) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                q[(j + kA) % 4] = fetch(min(z + j + kA, D2 - 1), o, c);
+                if (z + j < D2) {
+                    if (j % 2 == 0) s_T[(z + j) / 2][tid] = T;
+                    const float4 s = blend_taps<DT>(tap_weights(q[j].fx, q[j].fy), q[j].t);
+                    const float wgt = T * s.w;
+                    c0 = __builtin_fmaf(wgt, s.x, c0);
+                    c1 = __builtin_fmaf(wgt, s.y, c1);
+                    c2 = __builtin_fmaf(wgt, s.z, c2);
+                    T *= 1.0f - s.w;
+                }
+            }
         }
     }
-    float g0 = 0.0f, g1 = 0.0f, g2 = 0.0f;
-    if (ray) {
+    float g0 = 0.0f, g1 = 0.0f, g2 = 0.0f, sq = 0.0f;
+    if (own) {
         const size_t pix = ((size_t)view * H + y) * W + x;
         if (images) {
             const float d0 = c0 - images[3 * pix + 0];
@@ -601,63 +721,119 @@ __global__ __launch_bounds__(kBlock) void k_grad(const void* __restrict__ mpi, i
             g2 = dimg[3 * pix + 2];
         }
     }
+    const uint64_t full = plane_bits(D);
+    const auto mask_rs = row_rsrc(reinterpret_cast<const char*>(mask), mask ? HW * 8 : 0);
+    // the half of a cell's mask word that holds plane z, 0 (nothing selected) outside the plane;
+    // o: the cell's byte offset in a plane
+    auto mask_of = [&](unsigned o, int z) -> unsigned {
+        if (!mask) return o < (unsigned)plane_bytes ? ~0u : 0u;
+        return __builtin_amdgcn_raw_buffer_load_b32(mask_rs, o / (unsigned)(S / 8), z >= 32 ? 4 : 0, 0);
+    };
+    GradSink sink{&s_stage[wv], slots, mask, full, lane, HW, kcap, 0, 0};
+    constexpr int kNone = INT_MIN;
     float b0 = 0.0f, b1 = 0.0f, b2 = 0.0f;   // composite behind plane z
+    for (int zb = D2 - 2; zb >= 0; zb -= 2) {
+        float4 sm[2];
+        float fx[2], fy[2], Tz[2];
+        TapCell cell[2];
+        bool s00[2], s10[2], s01[2], s11[2];                // which of the four cells are selected
+        {
+            Fetched f[2];
+            unsigned m[2][4];
 #pragma unroll
-    for (int zz = 0; zz < MAXD; ++zz) {
-        const int z = MAXD - 1 - zz;
-        if (z < D) {
-            const Taps tp = make_taps(sw[z], x, y, H, W);
-            const float4 s = sample<DT>(mpi, z * HW, tp);
-            const float Tz = Ts[z];
-            const float ca = s.w * Tz;
-            float4 gs;
-            gs.x = g0 * ca;
-            gs.y = g1 * ca;
-            gs.z = g2 * ca;
-            gs.w = Tz * (g0 * (s.x - b0) + g1 * (s.y - b1) + g2 * (s.z - b2));
+            for (int j = 0; j < 2; ++j) {
+                TapOffs o;
+                f[j] = fetch(zb + j, o, cell[j]);
+                m[j][0] = mask_of(o.o00, zb + j);
+                m[j][1] = mask_of(o.o10, zb + j);
+                m[j][2] = mask_of(o.o01, zb + j);
+                m[j][3] = mask_of(o.o11, zb + j);
+            }
+            float t = s_T[zb / 2][tid];
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                sm[j] = blend_taps<DT>(tap_weights(f[j].fx, f[j].fy), f[j].t);
+                fx[j] = f[j].fx;
+                fy[j] = f[j].fy;
+                const unsigned bit = 1u << ((zb + j) & 31);
+                s00[j] = (m[j][0] & bit) != 0u;
+                s10[j] = (m[j][1] & bit) != 0u;
+                s01[j] = (m[j][2] & bit) != 0u;
+                s11[j] = (m[j][3] & bit) != 0u;
+                Tz[j] = t;
+                t *= 1.0f - sm[j].w;
+            }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int j = 1; j >= 0; --j) {
+            const int z = zb + j;
+            const float4 s = sm[j];
+            // (the buffers of the row merge alternate by plane: the next plane's writes go to
+            // the other)
+            int key = kNone;
+            float4 v00, v01, v10, v11;
+            int right = kNone;
+            bool keep = false;
+            // a wave none of whose cells is selected has nothing to add, nor to pass on
+            const bool some = __builtin_amdgcn_ballot_w64(s00[j] | s10[j] | s01[j] | s11[j]) != 0;
+            if (some) {
+                const float ca = s.w * Tz[j];
+                float4 gs;
+                gs.x = g0 * ca;
+                gs.y = g1 * ca;
+                gs.z = g2 * ca;
+                gs.w = Tz[j] * (g0 * (s.x - b0) + g1 * (s.y - b1) + g2 * (s.z - b2));
+                const TapW w = tap_weights(fx[j], fy[j]);
+                const unsigned in = cell[j].in;
+                key = (in & 1u) ? cell[j].cell : kNone;
+                right = (in & 2u) && own && fx[j] != 0.0f ? cell[j].cell + 1 : kNone;
+                v00 = scale4(w.w00, gs);
+                v01 = scale4(w.w01, gs);
+                v10 = scale4(w.w10, gs);
+                v11 = scale4(w.w11, gs);
+                if (__builtin_amdgcn_ballot_w64(fy[j] == 0.0f)) {   // no weight below: nothing, whatever the adjoint
+                    v01 = only_if(fy[j] != 0.0f, v01);
+                    v11 = only_if(fy[j] != 0.0f, v11);
+                }
+                // lane i takes lane i-1's right column where it is its own left column; where it
+                // is not, lane i-1 adds it to the cells by itself and sends zeros
+                const bool sent = (lane_next_i(key, kNone) == right) & (right != kNone);
+                keep = !sent & (right != kNone);
+                float4 w10 = v10, w11 = v11;
+                if (__builtin_amdgcn_ballot_w64(!sent) & (~0ull >> 1)) {
+                    w10 = only_if(sent, v10);
+                    w11 = only_if(sent, v11);
+                }
+                v00 = add4(v00, lane_prev_f4(w10));
+                v01 = add4(v01, lane_prev_f4(w11));
+                s_low[j][tid] = v01;
+            }
+            s_key[j][tid] = key;
             const float oa = 1.0f - s.w;
             b0 = s.w * s.x + oa * b0;
             b1 = s.w * s.y + oa * b1;
             b2 = s.w * s.z + oa * b2;
-            // the four taps (cell -1: no contribution): left column 00 / 01, right 10 / 11
-            int e00 = ray && tp.w00 != 0.0f ? tp.i00 : -1, e10 = ray && tp.w10 != 0.0f ? tp.i10 : -1;
-            int e01 = ray && tp.w01 != 0.0f ? tp.i01 : -1, e11 = ray && tp.w11 != 0.0f ? tp.i11 : -1;
-            float4 v00 = make_float4(tp.w00 * gs.x, tp.w00 * gs.y, tp.w00 * gs.z, tp.w00 * gs.w);
-            const float4 v10 = make_float4(tp.w10 * gs.x, tp.w10 * gs.y, tp.w10 * gs.z, tp.w10 * gs.w);
-            float4 v01 = make_float4(tp.w01 * gs.x, tp.w01 * gs.y, tp.w01 * gs.z, tp.w01 * gs.w);
-            const float4 v11 = make_float4(tp.w11 * gs.x, tp.w11 * gs.y, tp.w11 * gs.z, tp.w11 * gs.w);
-            // a right-column cell of lane i-1 that is lane i's left-column cell is added by
-            // lane i, once (the same equality on both sides: lane i merges exactly what lane
-            // i-1 drops), so neighbouring lanes of one atomic instruction rarely share a cell
-            const int p10 = lane_prev_i(e10, -1), p11 = lane_prev_i(e11, -1);
-            const float4 q10 = lane_prev_f4(v10), q11 = lane_prev_f4(v11);
-            const int n00 = lane_next_i(e00, -1), n01 = lane_next_i(e01, -1);
-            if (e00 >= 0 && p10 == e00) v00 = make_float4(v00.x + q10.x, v00.y + q10.y, v00.z + q10.z, v00.w + q10.w);
-            if (e01 >= 0 && p11 == e01) v01 = make_float4(v01.x + q11.x, v01.y + q11.y, v01.z + q11.z, v01.w + q11.w);
-            if (e10 >= 0 && n00 == e10) e10 = -1;
-            if (e11 >= 0 && n01 == e11) e11 = -1;
-            // the same between rows: a bottom-left cell of the wave above (same lane) that is
-            // this lane's top-left cell is added here, and dropped there
-            const int par = z & 1, t = threadIdx.x, wv = t >> 6;
-            s_cell[par][0][t] = e00;
-            s_cell[par][1][t] = e01;
-            s_low[par][t] = v01;
-            __syncthreads();   // (buffers alternate by plane: the next plane's writes go to the other)
-            if (wv > 0 && e00 >= 0 && s_cell[par][1][t - 64] == e00) {
-                const float4 a = s_low[par][t - 64];
-                v00 = make_float4(v00.x + a.x, v00.y + a.y, v00.z + a.z, v00.w + a.w);
+            __syncthreads();
+            if (some) {
+                if (wv > 0) {
+                    const int above = s_key[j][tid - 64];
+                    v00 = add4(v00, only_if((above != kNone) & (above + W == key), s_low[j][tid - 64]));
+                }
+                // what this wave adds: its upper left cells, a lower row that the row below does
+                // not take, and right columns that were not sent
+                const bool low = s01[j] & !(wv + 1 < kGenY && s_key[j][min(tid + 64, kGenThreads - 1)] == key + W);
+                sink.put(s00[j], z, key, v00);
+                sink.put(low, z, key + W, v01);
+                sink.put(keep & s10[j], z, right, v10);
+                sink.put(keep & s11[j], z, right + W, v11);
             }
-            if (wv + 1 < kTileH && e01 >= 0 && s_cell[par][0][t + 64] == e01) e01 = -1;
-            scatter_cell(slots, mask, full, kcap, HW, z, e00, v00);
-            scatter_cell(slots, mask, full, kcap, HW, z, e10, v10);
-            scatter_cell(slots, mask, full, kcap, HW, z, e01, v01);
-            scatter_cell(slots, mask, full, kcap, HW, z, e11, v11);
         }
     }
+    while (sink.count > 0) sink.flush(min(sink.count, 64));
     if (partials) {
         const float tot = block_sum(sq, sred);
-        if (threadIdx.x == 0)
-            partials[((size_t)view * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x] = tot;
+        if (threadIdx.x == 0) partials[tile] = tot;
     }
 }
 
@@ -1871,13 +2047,21 @@ int launch_grad_step(const hsgd_mpi& m, const hsgd_views& v, const uint64_t* mas
             hipLaunchKernelGGL(k_fill_zero, dim3((unsigned)std::min<int64_t>(ceil_div(n, 256), 8192)), dim3(256), 0, s,
                                slots, n);
         }
-        const dim3 grid((unsigned)ceil_div(m.W, kTileW), (unsigned)ceil_div(m.H, kTileH), (unsigned)v.N);
-        nparts = (int64_t)grid.x * grid.y * grid.z;
+        const int ntx = (int)ceil_div(m.W, kGenOX);
+        nparts = ceil_div(m.H, kGenY) * ntx * v.N;
+        const dim3 grid((unsigned)nparts);
         ProfScope ps(HSGD_K_GRAD, s);
-        HSGD_DISPATCH_T(m.dtype, HSGD_DISPATCH_D(m.D, hipLaunchKernelGGL((k_grad<DT, MD>), grid, dim3(kBlock), 0, s,
-                                                                        m.rgba, m.D, m.H, m.W, v.warps, v.images, dimg,
-                                                                        mask, kcap, inv_n, slots,
-                                                                        out_loss ? partials : nullptr)));
+        const float* im = v.images;
+        float* parts = out_loss ? partials : nullptr;
+#define HSGD_GRAD_GENERAL(MD)                                                                                       \
+    HSGD_DISPATCH_T(m.dtype, hipLaunchKernelGGL((k_grad<DT, MD>), grid, dim3(kGenThreads), 0, s, m.rgba, m.D, m.H, m.W, \
+                                                v.N, v.warps, im, dimg, mask, kcap, inv_n, slots, parts, ntx))
+        if (m.D <= 32) {
+            HSGD_GRAD_GENERAL(32);
+        } else {
+            HSGD_GRAD_GENERAL(64);
+        }
+#undef HSGD_GRAD_GENERAL
     }
     const int do_update = (lr_rgb != 0.0f || lr_alpha != 0.0f) ? 1 : 0;
     if (do_update || grad_out || out_loss) {
