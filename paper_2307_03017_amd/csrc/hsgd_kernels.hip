@@ -882,19 +882,32 @@ __device__ __forceinline__ float lerp_taps(float a0, float a1, const float4& wt)
 
 // One 64 x 8 tile of one view (tile = view + N * (tx + ntx * ty)); every thread of the
 // workgroup calls it.
-// Planes whose front-to-back samples the gradient tile keeps for its back-to-front scan,
-// and the waves per SIMD the kernel is compiled for: up to 32 planes 6 (3 workgroups per CU,
-// within 80 registers), except FP32 at 32 planes, which keeps the samples of its last 16
-// planes in the registers of 4 waves per SIMD (2 workgroups per CU) and measured faster.
-// 64 planes run at 4 waves per SIMD (their LDS allows 2 workgroups per CU); BF16 there
-// keeps 4 planes within that register budget.
+// The tile's forms by plane-count class: the planes whose front-to-back samples it keeps in
+// registers for its back-to-front scan (keep), the leading planes whose transmittance lives
+// in LDS instead of registers (tl), and the waves per SIMD it is compiled for. Small classes
+// (and BF16 at 32 planes) keep nothing and run 6 waves per SIMD (3 workgroups per CU, within
+// 80 registers and 53 KB); the others keep as many samples as the registers of 4 waves per
+// SIMD hold without spills once 2 workgroups' 160 KB of LDS are filled with transmittances.
+// The forms are within a few percent of each other (BF16, 24 planes, 512 x 384, 4 views:
+// 85 us against 88 at 6 waves; 48 planes: 172 us against 179 without kept samples): the
+// kernel is bound by its vector instructions, some 130 per wave and plane and scan pair, so
+// what counts is to run no more planes than the MPI has (see maxd_class).
 template <int DT, int MAXD>
 constexpr int grad_shift_keep() {
-    return DT == HSGD_FP32 && MAXD == 32 ? 16 : (DT == HSGD_BF16 && MAXD == 64 ? 4 : 0);
+    if (MAXD <= 16 || (DT == HSGD_BF16 && MAXD == 32)) return 0;
+    if (MAXD <= 32) return 16;
+    if (MAXD == 40) return 12;
+    if (MAXD == 48) return DT == HSGD_FP32 ? 8 : 10;
+    return DT == HSGD_FP32 ? 4 : 6;
 }
 template <int DT, int MAXD>
 constexpr int grad_shift_waves() {
-    return grad_shift_keep<DT, MAXD>() > 0 ? 4 : (MAXD > 32 ? 1 : 6);
+    return grad_shift_keep<DT, MAXD>() > 0 ? 4 : 6;
+}
+template <int DT, int MAXD>
+constexpr int grad_shift_tl() {
+    if (grad_shift_keep<DT, MAXD>() == 0) return 6;
+    return MAXD <= 40 ? 18 : MAXD == 48 ? 15 : 11;
 }
 // The batched kernel's persistent loop needs registers of its own: it keeps 8 planes at FP32
 // and 32 planes, none elsewhere (the results do not depend on how many are kept).
@@ -902,8 +915,12 @@ template <int DT, int MAXD>
 constexpr int batch_grad_keep() {
     return DT == HSGD_FP32 && MAXD == 32 ? 8 : 0;
 }
+template <int DT, int MAXD>
+constexpr int batch_grad_tl() {
+    return MAXD <= 32 ? 6 : 0;
+}
 
-template <int DT, int MAXD, bool MASKED, int KEEP = grad_shift_keep<DT, MAXD>()>
+template <int DT, int MAXD, bool MASKED, int KEEP = grad_shift_keep<DT, MAXD>(), int TL = grad_shift_tl<DT, MAXD>()>
 __device__ __forceinline__ void grad_shift_tile(
     const void* __restrict__ mpi, int D, int H, int W, int N, const hsgd_warp* __restrict__ warps,
     const float* __restrict__ images, const float* __restrict__ dimg, const uint64_t* __restrict__ mask,
@@ -916,14 +933,10 @@ __device__ __forceinline__ void grad_shift_tile(
     __shared__ float2 s_f[MAXD];                            // per plane: the shift's fraction
     __shared__ uint32_t s_code[(MAXD + 3) / 4][kSX * kSY];  // rank bytes of 4 planes per thread
     // Transmittance in front of the first kTL planes: these live longest (from the start of
-    // the front-to-back scan to the end of the back-to-front one), so at 6 waves per SIMD
-    // they go to LDS instead of registers, which would otherwise spill to scratch memory
-    // (whose reloads wait for every load in flight, the look-ahead included). Six planes
-    // keep 32 planes within 80 registers at 6 waves per SIMD; with 49.5 KB of LDS three
-    // workgroups fit a CU. The 4-wave form that keeps 16 planes' samples has 80 KB per
-    // workgroup (two per CU): 18 planes of transmittance there (74 KB) make the registers
-    // for the kept samples.
-    constexpr int kTL = MAXD <= 32 ? (KEEP > 8 ? 18 : 6) : 0;
+    // the front-to-back scan to the end of the back-to-front one), so they go to LDS instead
+    // of registers, which would otherwise spill to scratch memory (whose reloads wait for
+    // every load in flight, the look-ahead included).
+    constexpr int kTL = TL;
     __shared__ float s_T[kTL > 0 ? kTL : 1][kSX * kSY];
     const int view = tile % N;
     const int t2 = tile / N;
@@ -1026,8 +1039,8 @@ __device__ __forceinline__ void grad_shift_tile(
     // which leaves room for a third plane; FP32 taps fill the same registers with two
     constexpr int kAhead = DT == HSGD_BF16 ? 3 : 2;
     // The samples of the last kKeep planes of the front-to-back scan stay in registers for
-    // the back-to-front scan, which starts with them: 2 kKeep fewer row loads per wave (FP32
-    // at 32 planes; the kernel then runs at 4 waves per SIMD, see grad_shift_waves).
+    // the back-to-front scan, which starts with them: 2 kKeep fewer row loads per wave (the
+    // kernel then runs at 4 waves per SIMD, see grad_shift_keep).
     constexpr int kKeep = KEEP;
     float4 Sk[kKeep > 0 ? kKeep : 1];
     // Every plane iteration starts with a branch on an opaque, always-true value: the block
@@ -1535,6 +1548,11 @@ __global__ __launch_bounds__(256) void k_upsample(const void* __restrict__ src, 
 
 constexpr int kUpWaves = 4;
 
+// Planes a wave of the fused kernels below loads together: its planes in whole groups.
+constexpr int up_group(int planes) {
+    return planes < 4 ? planes : planes % 4 == 0 ? 4 : planes % 3 == 0 ? 3 : 5;
+}
+
 // Upsampling fused with the first selection at the new level, for levels of few
 // workgroups. A block covers 64 output pixels (lane = pixel) and its four waves split the
 // planes: each upsamples and stores a
@@ -1548,7 +1566,7 @@ __global__ __launch_bounds__(64 * kUpWaves) void k_upsample_select(const void* _
                                                                    float tau, int rule,
                                                                    uint64_t* __restrict__ mask) {
     constexpr int kPW = (MAXD + kUpWaves - 1) / kUpWaves;   // planes per wave
-    constexpr int kG = kPW < 4 ? kPW : 4;                    // tap loads of kG planes in flight together
+    constexpr int kG = up_group(kPW);                        // tap loads of kG planes in flight together
     static_assert(kPW % kG == 0, "whole load groups");
     __shared__ float s_a[kUpWaves * kPW][64];
     const int n = 4 * w * h;
@@ -1625,7 +1643,7 @@ __global__ __launch_bounds__(64 * kUpWaves) void k_upsample_select_blk(const voi
                                                                        float tau, int rule,
                                                                        uint64_t* __restrict__ mask) {
     constexpr int kPW = (MAXD + kUpWaves - 1) / kUpWaves;   // planes per wave
-    constexpr int kG = kPW < 4 ? kPW : 4;                    // planes of loads in flight
+    constexpr int kG = up_group(kPW);                        // planes of loads in flight
     static_assert(kPW % kG == 0, "whole load groups");
     using AT = typename UpAlpha<DT>::T;
     __shared__ AT s_a[MAXD][kUpPix];
@@ -1907,7 +1925,7 @@ __global__ __launch_bounds__(kSX * kSY) __attribute__((amdgpu_waves_per_eu(
         // kept live across tiles
         unsigned tid = threadIdx.x;
         asm volatile("" : "+v"(tid));
-        grad_shift_tile<DT, MAXD, true, batch_grad_keep<DT, MAXD>()>(b.mpi, b.D, b.H, b.W, b.N, b.warps, b.images, nullptr, b.mask, b.kcap,
+        grad_shift_tile<DT, MAXD, true, batch_grad_keep<DT, MAXD>(), batch_grad_tl<DT, MAXD>()>(b.mpi, b.D, b.H, b.W, b.N, b.warps, b.images, nullptr, b.mask, b.kcap,
                                         1.0f / (float)b.N, b.slots, b.partials, b.ntx,
                                         g - t->pre[kk][sl], tid);
     }
@@ -1928,15 +1946,32 @@ __global__ __launch_bounds__(256) void k_batch_update(const BatchTable* __restri
     }
 }
 
-int maxd_class(int D) { return D <= 8 ? 8 : D <= 16 ? 16 : D <= 32 ? 32 : 64; }
+// Plane-count classes: the kernels unroll their plane loops to MAXD planes and run the
+// planes z >= D as transparent ones, at full cost, so the classes lie 8 apart up to 48. FP32,
+// 512 x 378 x 40 planes, 3 views: gradient 173 us as 64 planes, 121 as 40; selection 32 and
+// 24, upsampling with selection 45 and 35 (24 planes, 4 views: gradient 107 us as 32, 87).
+int maxd_class(int D) {
+    return D <= 8 ? 8 : D <= 16 ? 16 : D <= 24 ? 24 : D <= 32 ? 32 : D <= 40 ? 40 : D <= 48 ? 48 : 64;
+}
 
 #define HSGD_DISPATCH_D(D, BODY)                         \
     switch (maxd_class(D)) {                             \
         case 8: { constexpr int MD = 8; BODY; } break;   \
         case 16: { constexpr int MD = 16; BODY; } break; \
+        case 24: { constexpr int MD = 24; BODY; } break; \
         case 32: { constexpr int MD = 32; BODY; } break; \
+        case 40: { constexpr int MD = 40; BODY; } break; \
+        case 48: { constexpr int MD = 48; BODY; } break; \
         default: { constexpr int MD = 64; BODY; } break; \
     }
+
+// The batched kernels keep to four classes: each is one persistent launch per step,
+// whether or not a request in flight belongs to it.
+#define HSGD_DISPATCH_BATCH_D(D, BODY)                      \
+    if ((D) <= 8) { constexpr int MD = 8; BODY; }           \
+    else if ((D) <= 16) { constexpr int MD = 16; BODY; }    \
+    else if ((D) <= 32) { constexpr int MD = 32; BODY; }    \
+    else { constexpr int MD = 64; BODY; }
 
 #define HSGD_DISPATCH_T(dt, BODY)                                  \
     if ((dt) == HSGD_FP32) { constexpr int DT = HSGD_FP32; BODY; } \
@@ -2163,7 +2198,7 @@ int launch_convert(const void* src, int sdt, void* dst, int ddt, size_t n, hipSt
 int batch_grad_occupancy(int dtype, int cls) {
     int n = 0;
     hipError_t e = hipSuccess;
-    HSGD_DISPATCH_T(dtype, HSGD_DISPATCH_D(cls, e = hipOccupancyMaxActiveBlocksPerMultiprocessor(
+    HSGD_DISPATCH_T(dtype, HSGD_DISPATCH_BATCH_D(cls, e = hipOccupancyMaxActiveBlocksPerMultiprocessor(
                                                     &n, reinterpret_cast<const void*>(&k_batch_grad<DT, MD>),
                                                     kSX * kSY, 0)));
     return e == hipSuccess ? n : 0;
@@ -2175,7 +2210,7 @@ static void enqueue_batch(const BatchTable* t, const BatchLaunch& c, hipStream_t
     for (int stage = 0; stage < kMaxBatchLevels - 1; ++stage)
         hipLaunchKernelGGL(k_batch_down, small, dim3(256), 0, s, t, stage);
     hipLaunchKernelGGL((k_batch_up<DT>), small, dim3(256), 0, s, t);
-    HSGD_DISPATCH_D(c.max_d, hipLaunchKernelGGL((k_batch_select<DT, MD>), small, dim3(256), 0, s, t));
+    HSGD_DISPATCH_BATCH_D(c.max_d, hipLaunchKernelGGL((k_batch_select<DT, MD>), small, dim3(256), 0, s, t));
     if (c.max_class >= 8)
         hipLaunchKernelGGL((k_batch_grad<DT, 8>), dim3((unsigned)c.grid_grad[0]), grad, 0, s, t, (int)BK_GRAD8);
     if (c.max_class >= 16)
