@@ -188,19 +188,16 @@ void fill_table(hsgd_batch* b, BatchTable* t, std::vector<int>& order) {
         const bool pyramid = s.step == 0;
         const int64_t HW = (int64_t)m.H * m.W;
         int items[BK_COUNT] = {};
-        if (pyramid) {
-            for (int st = 0; st < r.L - 1; ++st) {
-                const int src = r.L - 1 - st;
-                const hsgd_mpi& ms = r.levels[src];
-                d.pyr_src[st] = r.views[src].images;
-                d.pyr_dst[st] = const_cast<float*>(r.views[src - 1].images);
-                d.pyr_h[st] = ms.H;
-                d.pyr_w[st] = ms.W;
-                items[BK_DOWN0 + st] = r.views[src].N * (int)ceil_div((int64_t)(ms.H / 2) * (ms.W / 2), 256);
-            }
+        items[BK_FRONT] = d.front_main = up ? (int)ceil_div(d.uw, kUpCols) * d.uh : (int)ceil_div(HW, 256);
+        if (pyramid && r.L > 1) {
+            const hsgd_mpi& top = r.levels[r.L - 1];
+            d.pyr_nl = r.L - 1;
+            d.pyr_src = r.views[r.L - 1].images;
+            for (int j = 0; j < d.pyr_nl; ++j) d.pyr_dst[j] = const_cast<float*>(r.views[r.L - 2 - j].images);
+            d.pyr_h = top.H;
+            d.pyr_w = top.W;
+            items[BK_FRONT] += d.N * (int)ceil_div((int64_t)(top.H >> d.pyr_nl) * (top.W >> d.pyr_nl), 256);
         }
-        if (up) items[BK_UP] = m.D * (int)ceil_div(4LL * d.uh * d.uw, 256);
-        items[BK_SELECT] = (int)ceil_div(HW, 256);
         const int cls = maxd_class_host(m.D);
         const int gk = cls == 8 ? BK_GRAD8 : cls == 16 ? BK_GRAD16 : cls == 32 ? BK_GRAD32 : BK_GRAD64;
         items[gk] = d.ntx * d.nty * d.N;

@@ -24,6 +24,8 @@ constexpr int kShiftOY = 7;
 // supplies the right-hand taps of lane 62).
 constexpr int kShiftRX = 63;
 constexpr int kShiftRY = 8;
+// Source columns of one 2 x 2 upsampling workgroup (a wave less its two halo lanes).
+constexpr int kUpCols = 62;
 
 inline size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
@@ -148,9 +150,8 @@ constexpr int kMaxBatchLevels = 4;
 // The fixed kernel sequence of one batched step; each kernel walks a flat list of work
 // items (workgroup-sized pieces) concatenated over the slots it applies to.
 enum BatchKernel {
-    BK_DOWN0 = 0, BK_DOWN1, BK_DOWN2,            // target pyramid, finest level downwards
-    BK_UP,                                        // MPI upsampling into the current level
-    BK_SELECT,                                    // plane mask of the current level
+    BK_FRONT = 0,                                 // plane mask of the current level (with the upsampling
+                                                  // into it at its start), and the target pyramid
     BK_GRAD8, BK_GRAD16, BK_GRAD32, BK_GRAD64,    // gradient tiles, by plane-count class
     BK_UPDATE,                                    // sparse update + loss of the iteration
     BK_COUNT
@@ -166,9 +167,10 @@ struct BatchSlot {
     float4* slots;                    // gradient slots [N][kcap][H][W]
     float* partials;                  // loss partials [ntx * nty * N]
     float* loss_out;                  // loss of this iteration (or null)
-    const float* pyr_src[kMaxBatchLevels - 1];   // pyramid stages of the first step
-    float* pyr_dst[kMaxBatchLevels - 1];
-    int pyr_h[kMaxBatchLevels - 1], pyr_w[kMaxBatchLevels - 1];   // source shapes
+    const float* pyr_src;                        // first step: the finest targets [N][pyr_h][pyr_w][3]
+    float* pyr_dst[kMaxBatchLevels - 1];         // and the pyr_nl levels below them
+    int pyr_h, pyr_w, pyr_nl;
+    int front_main;                   // front items before the pyramid's
     int D, H, W, N;
     int uh, uw;                       // upsampling source shape
     int k, kcap, ntx, nty;

@@ -910,14 +910,21 @@ constexpr int grad_shift_tl() {
     return MAXD <= 40 ? 18 : MAXD == 48 ? 15 : 11;
 }
 // The batched kernel's persistent loop needs registers of its own: it keeps 8 planes at FP32
-// and 32 planes, none elsewhere (the results do not depend on how many are kept).
+// and 32 planes, none elsewhere (the results do not depend on how many are kept), and BF16
+// at 32 planes moves two more planes of transmittance to LDS to stay within the 80 registers
+// of 6 waves per SIMD (the eight requests of k_batch_front at their finest level: 1480 us at
+// 82 registers and 4 waves, 1425 at 6).
 template <int DT, int MAXD>
 constexpr int batch_grad_keep() {
     return DT == HSGD_FP32 && MAXD == 32 ? 8 : 0;
 }
 template <int DT, int MAXD>
+constexpr int batch_grad_waves() {
+    return MAXD <= 16 ? 1 : MAXD == 32 && DT == HSGD_BF16 ? 6 : MAXD == 32 ? 4 : 1;
+}
+template <int DT, int MAXD>
 constexpr int batch_grad_tl() {
-    return MAXD <= 32 ? 6 : 0;
+    return MAXD > 32 ? 0 : DT == HSGD_BF16 && MAXD == 32 ? 8 : 6;
 }
 
 template <int DT, int MAXD, bool MASKED, int KEEP = grad_shift_keep<DT, MAXD>(), int TL = grad_shift_tl<DT, MAXD>()>
@@ -1607,7 +1614,6 @@ __global__ __launch_bounds__(64 * kUpWaves) void k_upsample_select(const void* _
 // (the same source voxels, the same expression). The four waves split the planes and put
 // the alpha they stored (storage-rounded) in LDS; then each wave scores and selects a
 // quarter of the 248 output pixels front to back, as k_select does on the stored level.
-constexpr int kUpCols = 62;               // owner source columns per workgroup
 // Below this many workgroups (8 per CU) the 2 x 2 kernel has too few waves to hide its
 // longer per-wave work, and the per-pixel kernel is the faster one.
 constexpr int64_t kUpBlkMinGroups = 2048;
@@ -1637,20 +1643,18 @@ __device__ __forceinline__ float4 pick4(bool c, const float4& a, const float4& b
     return make_float4(c ? a.x : b.x, c ? a.y : b.y, c ? a.z : b.z, c ? a.w : b.w);
 }
 
+// Block bx of source row Y; every thread of the workgroup calls it.
 template <int DT, int MAXD>
-__global__ __launch_bounds__(64 * kUpWaves) void k_upsample_select_blk(const void* __restrict__ src, int D, int h,
-                                                                       int w, void* __restrict__ dst, int k,
-                                                                       float tau, int rule,
-                                                                       uint64_t* __restrict__ mask) {
+__device__ __forceinline__ void upsample_select_block(const void* __restrict__ src, int D, int h, int w,
+                                                      void* __restrict__ dst, int k, float tau, int rule,
+                                                      uint64_t* __restrict__ mask, int bx, int Y,
+                                                      typename UpAlpha<DT>::T (*__restrict__ s_a)[kUpPix]) {
     constexpr int kPW = (MAXD + kUpWaves - 1) / kUpWaves;   // planes per wave
     constexpr int kG = up_group(kPW);                        // planes of loads in flight
     static_assert(kPW % kG == 0, "whole load groups");
-    using AT = typename UpAlpha<DT>::T;
-    __shared__ AT s_a[MAXD][kUpPix];
     const int lane = threadIdx.x & 63;
     const int q = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    const int Y = blockIdx.y;
-    const int X = (int)blockIdx.x * kUpCols - 1 + lane;
+    const int X = bx * kUpCols - 1 + lane;
     const int Xc = min(max(X, 0), w - 1);
     const bool own = lane >= 1 && lane <= kUpCols && X < w;
     const int hw = h * w, W2 = 2 * w, n = 4 * hw;
@@ -1684,20 +1688,22 @@ __global__ __launch_bounds__(64 * kUpWaves) void k_upsample_select_blk(const voi
     const bool inner = __builtin_amdgcn_ballot_w64(own && !(xl0 && !xr0 && xr1)) == 0 && yu0 && !yd0 && yd1;
     const int out0 = 2 * Y * W2 + 2 * X;    // output voxel (2Y, 2X) of plane 0
     const int pix = 2 * (lane - 1);         // LDS column of output pixel (2Y, 2X)
+    // wave q takes the planes z = q mod 4, so that the waves share any D evenly
 #pragma unroll
     for (int j0 = 0; j0 < kPW; j0 += kG) {
+        if (j0 * kUpWaves + q >= D) break;
         float4 m[kG][3];
 #pragma unroll
         for (int j = 0; j < kG; ++j) {
             // plane index clamped, so the loads need no guard
-            const int base = min(q * kPW + j0 + j, D - 1) * hw;
+            const int base = min((j0 + j) * kUpWaves + q, D - 1) * hw;
             m[j][0] = Vox<DT>::load(src, base + row0);
             m[j][1] = Vox<DT>::load(src, base + row1);
             m[j][2] = Vox<DT>::load(src, base + row2);
         }
 #pragma unroll
         for (int j = 0; j < kG; ++j) {
-            const int z = q * kPW + j0 + j;
+            const int z = (j0 + j) * kUpWaves + q;
             float4 L[3], R[3];
 #pragma unroll
             for (int r = 0; r < 3; ++r) {
@@ -1740,7 +1746,7 @@ __global__ __launch_bounds__(64 * kUpWaves) void k_upsample_select_blk(const voi
     __syncthreads();
     // selection: output pixel e of the workgroup (row 2Y + e / 124, column 2 X0 + e % 124)
     const int e = q * 64 + lane;
-    const int ox = 2 * (int)blockIdx.x * kUpCols + e % (kUpPix / 2);
+    const int ox = 2 * bx * kUpCols + e % (kUpPix / 2);
     if (e < kUpPix && ox < W2) {
         const int oy = 2 * Y + e / (kUpPix / 2);
         float A[MAXD];
@@ -1750,6 +1756,16 @@ __global__ __launch_bounds__(64 * kUpWaves) void k_upsample_select_blk(const voi
             if (z < D) A[z] = score_step(UpAlpha<DT>::get(s_a[z][e]), T);
         mask[oy * W2 + ox] = topk_bits<MAXD>(A, D, k, tau, rule);
     }
+}
+
+template <int DT, int MAXD>
+__global__ __launch_bounds__(64 * kUpWaves) void k_upsample_select_blk(const void* __restrict__ src, int D, int h,
+                                                                       int w, void* __restrict__ dst, int k,
+                                                                       float tau, int rule,
+                                                                       uint64_t* __restrict__ mask, int nbx) {
+    __shared__ typename UpAlpha<DT>::T s_a[MAXD][kUpPix];
+    const int g = blockIdx.x;
+    upsample_select_block<DT, MAXD>(src, D, h, w, dst, k, tau, rule, mask, g % nbx, g / nbx, s_a);
 }
 
 // The 2x2 box mean of a (x, y), b (x + 1, y), c (x, y + 1), d (x + 1, y + 1): the one
@@ -1869,42 +1885,45 @@ __device__ __forceinline__ int batch_slot_of(const BatchTable* __restrict__ t, i
     return __builtin_amdgcn_readfirstlane(s);
 }
 
-__global__ __launch_bounds__(256) void k_batch_down(const BatchTable* __restrict__ t, int stage) {
-    const int kk = BK_DOWN0 + stage;
-    const int total = t->total[kk];
-    for (int g = blockIdx.x; g < total; g += gridDim.x) {
-        const int sl = batch_slot_of(t, kk, g);
-        const BatchSlot& b = t->slot[sl];
-        const int j = g - t->pre[kk][sl];
-        const int H = b.pyr_h[stage], W = b.pyr_w[stage];
-        const int nb = ((H / 2) * (W / 2) + 255) / 256;
-        const int n = j / nb;
-        downsample_pixel(b.pyr_src[stage], H, W, b.pyr_dst[stage], n, (j - n * nb) * 256 + threadIdx.x);
-    }
-}
-
-template <int DT>
-__global__ __launch_bounds__(256) void k_batch_up(const BatchTable* __restrict__ t) {
-    const int total = t->total[BK_UP];
-    for (int g = blockIdx.x; g < total; g += gridDim.x) {
-        const int sl = batch_slot_of(t, BK_UP, g);
-        const BatchSlot& b = t->slot[sl];
-        const int j = g - t->pre[BK_UP][sl];
-        const int nb = (4 * b.uh * b.uw + 255) / 256;
-        const int z = j / nb;
-        upsample_voxel<DT>(b.up_src, b.uh, b.uw, b.mpi, z, (j - z * nb) * 256 + threadIdx.x);
-    }
-}
-
+// The front of a step, one launch for what does not depend on each other: the slots at the
+// start of a level above the coarsest upsample into it and select there (2 x 2 blocks, as
+// k_upsample_select_blk), the others select on the MPI they have, and a request's first step
+// also reduces its targets (as k_pyramid). A slot's first front_main items are the former,
+// the rest the pyramid's. Bound by memory traffic: the level is written once and its alphas
+// are scored from LDS. Eight requests (2 of 1008 x 756 x 32, 3 of 512 x 384 x 32, 3 of
+// 256 x 192 x 16, BF16), as three box means, upsampling by pixel and selection from the stored
+// level in five launches: 488 us at their finest level, 115 one below; here 212 and 65. (Items
+// in launch order: grouping them by XCD took 221 us.)
 template <int DT, int MAXD>
-__global__ __launch_bounds__(256) void k_batch_select(const BatchTable* __restrict__ t) {
-    const int total = t->total[BK_SELECT];
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MAXD <= 40 ? 4 : 2))) void k_batch_front(
+    const BatchTable* __restrict__ t) {
+    static_assert(64 * kUpWaves == 256, "one workgroup size");
+    __shared__ typename UpAlpha<DT>::T s_a[MAXD][kUpPix];
+    const int total = t->total[BK_FRONT];
     for (int g = blockIdx.x; g < total; g += gridDim.x) {
-        const int sl = batch_slot_of(t, BK_SELECT, g);
+        const int sl = batch_slot_of(t, BK_FRONT, g);
         const BatchSlot& b = t->slot[sl];
-        const int p = (g - t->pre[BK_SELECT][sl]) * 256 + threadIdx.x;
-        const int HW = b.H * b.W;
-        if (p < HW) b.mask[p] = select_bits<DT, MAXD>(b.mpi, b.D, HW, p, b.k, b.tau, b.rule);
+        const int j = g - t->pre[BK_FRONT][sl];
+        if (j >= b.front_main) {
+            const int e = j - b.front_main;
+            const int nb = ((b.pyr_h >> b.pyr_nl) * (b.pyr_w >> b.pyr_nl) + 255) / 256;
+            const int n = e / nb, bx = e - n * nb;
+            if (b.pyr_nl == 1)
+                pyramid_block<1>(b.pyr_src, b.pyr_h, b.pyr_w, b.pyr_dst[0], nullptr, nullptr, n, bx);
+            else if (b.pyr_nl == 2)
+                pyramid_block<2>(b.pyr_src, b.pyr_h, b.pyr_w, b.pyr_dst[0], b.pyr_dst[1], nullptr, n, bx);
+            else
+                pyramid_block<3>(b.pyr_src, b.pyr_h, b.pyr_w, b.pyr_dst[0], b.pyr_dst[1], b.pyr_dst[2], n, bx);
+        } else if (b.up_src) {
+            const int nbx = (b.uw + kUpCols - 1) / kUpCols;
+            __syncthreads();                 // the previous item's alphas are no longer read
+            upsample_select_block<DT, MAXD>(b.up_src, b.D, b.uh, b.uw, b.mpi, b.k, b.tau, b.rule, b.mask, j % nbx,
+                                            j / nbx, s_a);
+        } else {
+            const int p = j * 256 + threadIdx.x;
+            const int HW = b.H * b.W;
+            if (p < HW) b.mask[p] = select_bits<DT, MAXD>(b.mpi, b.D, HW, p, b.k, b.tau, b.rule);
+        }
     }
 }
 
@@ -1913,7 +1932,7 @@ __global__ __launch_bounds__(256) void k_batch_select(const BatchTable* __restri
 // budget as for k_grad_shift where the tile keeps samples.
 template <int DT, int MAXD>
 __global__ __launch_bounds__(kSX * kSY) __attribute__((amdgpu_waves_per_eu(
-    batch_grad_keep<DT, MAXD>() > 0 ? grad_shift_waves<DT, MAXD>() : 1))) void k_batch_grad(const BatchTable* __restrict__ t,
+    batch_grad_waves<DT, MAXD>()))) void k_batch_grad(const BatchTable* __restrict__ t,
                                                                                           int kk) {
     const int total = t->total[kk];
     for (int i = blockIdx.x; i < total; i += gridDim.x) {
@@ -2126,11 +2145,12 @@ int launch_upsample(const hsgd_mpi& c, const hsgd_mpi& f, hipStream_t s) {
 int launch_upsample_select(const hsgd_mpi& c, const hsgd_mpi& f, int k, float tau, int rule, uint64_t* mask,
                            hipStream_t s) {
     ProfScope ps(HSGD_K_UPSAMPLE, s);
-    const dim3 blk((unsigned)ceil_div(c.W, kUpCols), (unsigned)c.H);
-    if ((int64_t)blk.x * blk.y >= kUpBlkMinGroups) {
+    const int nbx = (int)ceil_div(c.W, kUpCols);
+    const dim3 blk((unsigned)((int64_t)nbx * c.H));
+    if ((int64_t)blk.x >= kUpBlkMinGroups) {
         HSGD_DISPATCH_T(c.dtype, HSGD_DISPATCH_D(c.D, hipLaunchKernelGGL((k_upsample_select_blk<DT, MD>), blk,
                                                                         dim3(64 * kUpWaves), 0, s, c.rgba, c.D, c.H,
-                                                                        c.W, f.rgba, k, tau, rule, mask)));
+                                                                        c.W, f.rgba, k, tau, rule, mask, nbx)));
     } else {
         const dim3 grid((unsigned)ceil_div((int64_t)f.H * f.W, 64));
         HSGD_DISPATCH_T(c.dtype, HSGD_DISPATCH_D(c.D, hipLaunchKernelGGL((k_upsample_select<DT, MD>), grid,
@@ -2207,10 +2227,7 @@ int batch_grad_occupancy(int dtype, int cls) {
 template <int DT>
 static void enqueue_batch(const BatchTable* t, const BatchLaunch& c, hipStream_t s) {
     const dim3 small((unsigned)c.grid_small), grad(kSX * kSY);
-    for (int stage = 0; stage < kMaxBatchLevels - 1; ++stage)
-        hipLaunchKernelGGL(k_batch_down, small, dim3(256), 0, s, t, stage);
-    hipLaunchKernelGGL((k_batch_up<DT>), small, dim3(256), 0, s, t);
-    HSGD_DISPATCH_BATCH_D(c.max_d, hipLaunchKernelGGL((k_batch_select<DT, MD>), small, dim3(256), 0, s, t));
+    HSGD_DISPATCH_D(c.max_d, hipLaunchKernelGGL((k_batch_front<DT, MD>), small, dim3(256), 0, s, t));
     if (c.max_class >= 8)
         hipLaunchKernelGGL((k_batch_grad<DT, 8>), dim3((unsigned)c.grid_grad[0]), grad, 0, s, t, (int)BK_GRAD8);
     if (c.max_class >= 16)
