@@ -322,9 +322,8 @@ hsgd_status hsgd_convert(const void* src, int32_t src_dtype, void* dst, int32_t 
  * stream (scene): its views and the initial MPI at the coarsest level, refined coarse to
  * fine exactly as hsgd_refine does. Requests that arrive while others are in flight are
  * admitted as slots and HBM budget allow; each hsgd_batch_step runs ONE iteration of
- * every request in flight, all of them in the same fixed sequence of persistent kernels
- * captured once in a HIP graph (the work of each request is a range of work items in a
- * device table rebuilt per step). A request's result is bitwise the result of hsgd_refine
+ * every request in flight, all of them in the same few kernels (the work of each request
+ * is a range of work items in a device table rebuilt per step). A request's result is bitwise the result of hsgd_refine
  * on the same inputs: the per-request arithmetic and its order are the same.
  *
  * Streams keep their buffers: the caller allocates, per stream, the MPI of every level
@@ -368,8 +367,8 @@ size_t hsgd_batch_workspace_bytes(const hsgd_batch_config* cfg);
 
 /* Creates a batch on the current device. ws is device memory of at least
  * hsgd_batch_workspace_bytes(cfg) bytes, owned by the caller and kept until
- * hsgd_batch_destroy. The library allocates only host-side state, two small pinned
- * staging buffers, events and (at the first step) the instantiated graph.
+ * hsgd_batch_destroy. The library allocates only host-side state, a few small pinned
+ * staging buffers and events.
  * HSGD_E_BUDGET if the workspace alone exceeds cfg->hbm_budget. */
 hsgd_status hsgd_batch_create(const hsgd_batch_config* cfg, void* ws, size_t ws_bytes,
                               hsgd_batch** out);
@@ -383,8 +382,8 @@ hsgd_status hsgd_batch_destroy(hsgd_batch* b);
 hsgd_status hsgd_batch_admit(hsgd_batch* b, const hsgd_request* r, int64_t* ticket);
 
 /* Enqueues one iteration of every admitted request on stream (one table upload, one
- * graph launch). Blocks the host only while the step before the previous one still holds
- * its staging buffer. Steps run in the order they are enqueued whatever streams they are
+ * launch per kernel with work). Blocks the host only while the fourth step before it still runs (which
+ * holds its staging buffer). Steps run in the order they are enqueued whatever streams they are
  * given: a step enqueued on a stream other than the previous step's first makes that
  * stream wait for the previous step to complete (all steps share one device table, and
  * each continues the requests of the one before). Outputs (each may be NULL): *n_active requests stepped; the tickets

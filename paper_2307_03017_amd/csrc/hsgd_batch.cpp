@@ -4,9 +4,8 @@
 // its j-th step is iteration t of level l, preceded by the upsampling into level l when
 // t == 0 and l > 0, and, at j == 0, by the target pyramid. Each hsgd_batch_step advances
 // every request in flight by one such step. The host writes one BatchTable per step (the
-// per-request descriptors and, per kernel, the prefix counts of work items), uploads it
-// with one copy, and launches the captured graph of the fixed kernel sequence; each
-// persistent kernel walks the flat item list, so one graph serves any mix of requests.
+// per-request descriptors and, per kernel, the prefix counts of work items) and enqueues the
+// step's kernels, each over exactly its items: the requests of any mix share the launches.
 #include <hip/hip_runtime_api.h>
 
 #include <cmath>
@@ -21,6 +20,9 @@ using namespace hsgd;
 namespace {
 
 constexpr int kRing = 256;        // step events kept for completion queries
+// Staged tables: a buffer is written again when its step has completed, which that step's
+// own event tells (an event after each upload would cost the stream 6 us a step).
+constexpr int kStaging = 4;
 
 struct Slot {
     bool busy = false;
@@ -38,8 +40,6 @@ struct Stream {
     int64_t bytes = 0;
     bool in_flight = false;        // a frame with iterations not yet stepped
 };
-
-int maxd_class_host(int D) { return D <= 8 ? 8 : D <= 16 ? 16 : D <= 32 ? 32 : 64; }
 
 struct SlotWs {
     size_t mask_off, slots_off, partial_off, bytes;
@@ -89,6 +89,19 @@ int64_t resident_bytes(const hsgd_request& r) {
     return b;
 }
 
+// Makes a device current for a scope.
+struct OnDevice {
+    explicit OnDevice(int device) {
+        if (hipGetDevice(&prev) != hipSuccess || prev == device || hipSetDevice(device) != hipSuccess) prev = -1;
+    }
+    ~OnDevice() {
+        if (prev >= 0) (void)hipSetDevice(prev);
+    }
+    OnDevice(const OnDevice&) = delete;
+    OnDevice& operator=(const OnDevice&) = delete;
+    int prev = -1;
+};
+
 hsgd_status hip_status(hipError_t e, const char* what) {
     if (e == hipSuccess) return HSGD_OK;
     return fail(HSGD_E_HIP, "%s: %s", what, hipGetErrorString(e));
@@ -102,17 +115,12 @@ struct hsgd_batch {
     char* ws = nullptr;
     BatchTable* dev_table = nullptr;
     SlotWs sws{};
-    BatchLaunch launch{};
-    BatchTable* staging[2] = {nullptr, nullptr};     // pinned
-    hipEvent_t copy_done[2] = {nullptr, nullptr};
-    bool copy_used[2] = {false, false};
+    BatchTable* staging[kStaging] = {};              // pinned
     hipEvent_t step_ev[kRing] = {};
     double step_ms[kRing] = {};                       // harvested completion times
     bool step_harvested[kRing] = {};
     hipEvent_t ref = nullptr;
     bool have_ref = false;
-    hipGraphExec_t exec = nullptr;
-    hipStream_t capture = nullptr;                    // private stream the graph is captured on
     hipStream_t last_stream = nullptr;                // stream of the latest step (valid once steps > 0)
     int64_t steps = 0;
     std::vector<Slot> slots;
@@ -198,9 +206,7 @@ void fill_table(hsgd_batch* b, BatchTable* t, std::vector<int>& order) {
             d.pyr_w = top.W;
             items[BK_FRONT] += d.N * (int)ceil_div((int64_t)(top.H >> d.pyr_nl) * (top.W >> d.pyr_nl), 256);
         }
-        const int cls = maxd_class_host(m.D);
-        const int gk = cls == 8 ? BK_GRAD8 : cls == 16 ? BK_GRAD16 : cls == 32 ? BK_GRAD32 : BK_GRAD64;
-        items[gk] = d.ntx * d.nty * d.N;
+        items[BK_GRAD + batch_class(m.D)] = d.ntx * d.nty * d.N;
         items[BK_UPDATE] = (int)ceil_div(HW, 256);
         for (int k = 0; k < BK_COUNT; ++k) {
             t->pre[k][n + 1] = t->pre[k][n] + items[k];
@@ -243,29 +249,13 @@ hsgd_status hsgd_batch_create(const hsgd_batch_config* cfg, void* ws, size_t ws_
     b->slots.resize(cfg->max_slots);
     b->used = (int64_t)need;
     hipError_t e = hipGetDevice(&b->device);
-    int cus = 0;
-    if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, b->device);
-    for (int i = 0; i < 2 && e == hipSuccess; ++i)
-        e = hipHostMalloc(reinterpret_cast<void**>(&b->staging[i]), sizeof(BatchTable), hipHostMallocDefault);
-    for (int i = 0; i < 2 && e == hipSuccess; ++i) e = hipEventCreateWithFlags(&b->copy_done[i], hipEventDisableTiming);
+    for (int i = 0; i < kStaging && e == hipSuccess; ++i)
+        e = hipHostMalloc(reinterpret_cast<void**>(&b->staging[i]), sizeof(BatchTable), hipHostMallocCoherent);
     for (int i = 0; i < kRing && e == hipSuccess; ++i) e = hipEventCreate(&b->step_ev[i]);
     if (e == hipSuccess) e = hipEventCreate(&b->ref);
-    if (e == hipSuccess) e = hipStreamCreateWithFlags(&b->capture, hipStreamNonBlocking);
     if (e != hipSuccess) {
         hsgd_batch_destroy(b);
         return hip_status(e, fn);
-    }
-    BatchLaunch& L = b->launch;
-    L.dtype = cfg->dtype;
-    L.max_class = maxd_class_host(cfg->max_D);
-    L.max_n = cfg->max_N;
-    L.max_d = cfg->max_D;
-    // persistent grids: whole multiples of the CU count (so of the 8 XCDs)
-    L.grid_small = 8 * cus;
-    const int classes[4] = {8, 16, 32, 64};
-    for (int c = 0; c < 4; ++c) {
-        const int occ = classes[c] <= L.max_class ? batch_grad_occupancy(cfg->dtype, classes[c]) : 1;
-        L.grid_grad[c] = (occ > 0 ? occ : 1) * cus;
     }
     *out = b;
     return HSGD_OK;
@@ -276,16 +266,11 @@ hsgd_status hsgd_batch_destroy(hsgd_batch* b) {
     if (!b) return HSGD_OK;
     for (int i = 0; i < kRing; ++i)
         if (b->step_ev[i]) hipEventSynchronize(b->step_ev[i]);
-    for (int i = 0; i < 2; ++i) {
-        if (b->copy_done[i]) hipEventSynchronize(b->copy_done[i]);
-        if (b->copy_done[i]) hipEventDestroy(b->copy_done[i]);
+    for (int i = 0; i < kStaging; ++i)
         if (b->staging[i]) hipHostFree(b->staging[i]);
-    }
     for (int i = 0; i < kRing; ++i)
         if (b->step_ev[i]) hipEventDestroy(b->step_ev[i]);
     if (b->ref) hipEventDestroy(b->ref);
-    if (b->exec) hipGraphExecDestroy(b->exec);
-    if (b->capture) hipStreamDestroy(b->capture);
     delete b;
     return HSGD_OK;
 }
@@ -379,9 +364,10 @@ hsgd_status hsgd_batch_step(hsgd_batch* b, hipStream_t stream, int32_t* n_active
         if (b->slots[i].busy) order.push_back(i);
     if (order.empty()) return HSGD_OK;
 
-    const int cur = (int)(b->steps & 1);
+    BatchTable* const staged = b->staging[b->steps % kStaging];
     hipError_t e = hipSuccess;
-    if (b->copy_used[cur]) e = hipEventSynchronize(b->copy_done[cur]);   // the step before last
+    const OnDevice on(b->device);                    // kernels launch on the current device
+    if (b->steps >= kStaging) e = hipEventSynchronize(b->step_ev[(b->steps - kStaging) % kRing]);
     if (e != hipSuccess) return hip_status(e, fn);
     // the ring entry about to be reused: keep its completion time
     const int64_t old = b->steps - kRing;
@@ -392,28 +378,9 @@ hsgd_status hsgd_batch_step(hsgd_batch* b, hipStream_t stream, int32_t* n_active
         e = hipStreamWaitEvent(stream, b->step_ev[(int)((b->steps - 1) % kRing)], 0);
         if (e != hipSuccess) return hip_status(e, fn);
     }
-    fill_table(b, b->staging[cur], order);
-    e = hipMemcpyAsync(b->dev_table, b->staging[cur], sizeof(BatchTable), hipMemcpyHostToDevice, stream);
-    if (e == hipSuccess) e = hipEventRecord(b->copy_done[cur], stream);
-    if (e != hipSuccess) return hip_status(e, fn);
-    b->copy_used[cur] = true;
-    if (!b->exec) {
-        // captured once on the private stream (the caller's may be the legacy default
-        // stream, which cannot capture); launched on the caller's stream every step
-        hipGraph_t g = nullptr;
-        e = hipStreamBeginCapture(b->capture, hipStreamCaptureModeThreadLocal);
-        if (e != hipSuccess) return hip_status(e, fn);
-        const int le = launch_batch_step(b->dev_table, b->launch, b->capture);
-        e = hipStreamEndCapture(b->capture, &g);
-        if (le != hipSuccess) {
-            if (g) hipGraphDestroy(g);
-            return hip_status((hipError_t)le, fn);
-        }
-        if (e == hipSuccess) e = hipGraphInstantiate(&b->exec, g, nullptr, nullptr, 0);
-        if (g) hipGraphDestroy(g);
-        if (e != hipSuccess) return hip_status(e, fn);
-    }
-    e = hipGraphLaunch(b->exec, stream);
+    fill_table(b, staged, order);
+    e = (hipError_t)launch_batch_step(staged, b->dev_table, b->cfg.dtype, stream);
+    if (e != hipSuccess) (void)hipStreamSynchronize(stream);   // nothing may still read the staged table
     const int ri = (int)(b->steps % kRing);
     if (e == hipSuccess) e = hipEventRecord(b->step_ev[ri], stream);
     if (e != hipSuccess) return hip_status(e, fn);

@@ -147,13 +147,15 @@ int launch_convert(const void* src, int sdt, void* dst, int ddt, size_t n, hipSt
 // ---- batched serving step (hsgd_batch.cpp builds the table, hsgd_kernels.hip runs it) ----
 constexpr int kMaxSlots = 16;
 constexpr int kMaxBatchLevels = 4;
-// The fixed kernel sequence of one batched step; each kernel walks a flat list of work
-// items (workgroup-sized pieces) concatenated over the slots it applies to.
+// Plane-count classes the translation-path kernels are compiled for.
+constexpr int kNumClasses = 7;
+// The kernels of one batched step; each walks a flat list of work items (workgroup-sized
+// pieces) concatenated over the slots it applies to.
 enum BatchKernel {
-    BK_FRONT = 0,                                 // plane mask of the current level (with the upsampling
-                                                  // into it at its start), and the target pyramid
-    BK_GRAD8, BK_GRAD16, BK_GRAD32, BK_GRAD64,    // gradient tiles, by plane-count class
-    BK_UPDATE,                                    // sparse update + loss of the iteration
+    BK_FRONT = 0,                   // plane mask of the current level (with the upsampling into
+                                    // it at its start), and the target pyramid
+    BK_GRAD,                        // gradient tiles, one list per plane-count class
+    BK_UPDATE = BK_GRAD + kNumClasses,   // sparse update + loss of the iteration
     BK_COUNT
 };
 
@@ -180,7 +182,7 @@ struct BatchSlot {
     int pad_[3];
 };
 
-struct BatchTable {
+struct alignas(16) BatchTable {
     int nslot;
     int pad_[3];
     int total[BK_COUNT];                       // work items per kernel
@@ -188,16 +190,10 @@ struct BatchTable {
     BatchSlot slot[kMaxSlots];
 };
 
-struct BatchLaunch {
-    int dtype;
-    int max_class;                 // largest plane-count class admitted (8, 16, 32 or 64)
-    int max_n, max_d;              // bound the update kernel's LDS table
-    int grid_small;                // workgroups of the 256-thread kernels
-    int grid_grad[4];              // workgroups of the gradient kernels per class
-};
-// Enqueue the fixed sequence of batched kernels reading `table` (device memory).
-int launch_batch_step(const BatchTable* table, const BatchLaunch& cfg, hipStream_t s);
-// Workgroups per CU the batched gradient kernel of a class can keep resident.
-int batch_grad_occupancy(int dtype, int cls);
+// Enqueue the step `staged` (pinned host memory) describes, through its copy at `table`
+// (device memory).
+int launch_batch_step(const BatchTable* staged, BatchTable* table, int dtype, hipStream_t s);
+// Index of a plane count's class (0 .. kNumClasses - 1).
+int batch_class(int D);
 
 }  // namespace hsgd

@@ -909,24 +909,6 @@ constexpr int grad_shift_tl() {
     if (grad_shift_keep<DT, MAXD>() == 0) return 6;
     return MAXD <= 40 ? 18 : MAXD == 48 ? 15 : 11;
 }
-// The batched kernel's persistent loop needs registers of its own: it keeps 8 planes at FP32
-// and 32 planes, none elsewhere (the results do not depend on how many are kept), and BF16
-// at 32 planes moves two more planes of transmittance to LDS to stay within the 80 registers
-// of 6 waves per SIMD (the eight requests of k_batch_front at their finest level: 1480 us at
-// 82 registers and 4 waves, 1425 at 6).
-template <int DT, int MAXD>
-constexpr int batch_grad_keep() {
-    return DT == HSGD_FP32 && MAXD == 32 ? 8 : 0;
-}
-template <int DT, int MAXD>
-constexpr int batch_grad_waves() {
-    return MAXD <= 16 ? 1 : MAXD == 32 && DT == HSGD_BF16 ? 6 : MAXD == 32 ? 4 : 1;
-}
-template <int DT, int MAXD>
-constexpr int batch_grad_tl() {
-    return MAXD > 32 ? 0 : DT == HSGD_BF16 && MAXD == 32 ? 8 : 6;
-}
-
 template <int DT, int MAXD, bool MASKED, int KEEP = grad_shift_keep<DT, MAXD>(), int TL = grad_shift_tl<DT, MAXD>()>
 __device__ __forceinline__ void grad_shift_tile(
     const void* __restrict__ mpi, int D, int H, int W, int N, const hsgd_warp* __restrict__ warps,
@@ -1878,11 +1860,20 @@ __global__ __launch_bounds__(256) void k_convert(const void* __restrict__ src, v
 // ------------------------------------------------------------------------------------
 // batched serving step: persistent kernels over the work items of every in-flight request
 // ------------------------------------------------------------------------------------
+// Each kernel is launched over exactly its items of the step: workgroup g takes item g of
+// the list concatenated over the requests.
 // Slot of flat work item g of kernel kk (prefix counts are non-decreasing; uniform result).
 __device__ __forceinline__ int batch_slot_of(const BatchTable* __restrict__ t, int kk, int g) {
     int s = 0;
     for (int j = 1; j < t->nslot; ++j) s += g >= t->pre[kk][j] ? 1 : 0;
     return __builtin_amdgcn_readfirstlane(s);
+}
+
+// The step's table from the pinned memory it was written to: a kernel on the stream's own
+// queue, 10 us between two steps' work with the step's event (a copy engine's hand-over and
+// an event that frees the staging buffer: 15).
+__global__ __launch_bounds__(256) void k_batch_table(const uint4* __restrict__ src, uint4* __restrict__ dst, int n) {
+    for (int i = threadIdx.x; i < n; i += 256) dst[i] = src[i];
 }
 
 // The front of a step, one launch for what does not depend on each other: the slots at the
@@ -1895,82 +1886,66 @@ __device__ __forceinline__ int batch_slot_of(const BatchTable* __restrict__ t, i
 // level in five launches: 488 us at their finest level, 115 one below; here 212 and 65. (Items
 // in launch order: grouping them by XCD took 221 us.)
 template <int DT, int MAXD>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MAXD <= 40 ? 4 : 2))) void k_batch_front(
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(DT == HSGD_FP32 && MAXD > 16 ? 2 : 4))) void k_batch_front(
     const BatchTable* __restrict__ t) {
     static_assert(64 * kUpWaves == 256, "one workgroup size");
     __shared__ typename UpAlpha<DT>::T s_a[MAXD][kUpPix];
-    const int total = t->total[BK_FRONT];
-    for (int g = blockIdx.x; g < total; g += gridDim.x) {
-        const int sl = batch_slot_of(t, BK_FRONT, g);
-        const BatchSlot& b = t->slot[sl];
-        const int j = g - t->pre[BK_FRONT][sl];
-        if (j >= b.front_main) {
-            const int e = j - b.front_main;
-            const int nb = ((b.pyr_h >> b.pyr_nl) * (b.pyr_w >> b.pyr_nl) + 255) / 256;
-            const int n = e / nb, bx = e - n * nb;
-            if (b.pyr_nl == 1)
-                pyramid_block<1>(b.pyr_src, b.pyr_h, b.pyr_w, b.pyr_dst[0], nullptr, nullptr, n, bx);
-            else if (b.pyr_nl == 2)
-                pyramid_block<2>(b.pyr_src, b.pyr_h, b.pyr_w, b.pyr_dst[0], b.pyr_dst[1], nullptr, n, bx);
-            else
-                pyramid_block<3>(b.pyr_src, b.pyr_h, b.pyr_w, b.pyr_dst[0], b.pyr_dst[1], b.pyr_dst[2], n, bx);
-        } else if (b.up_src) {
-            const int nbx = (b.uw + kUpCols - 1) / kUpCols;
-            __syncthreads();                 // the previous item's alphas are no longer read
-            upsample_select_block<DT, MAXD>(b.up_src, b.D, b.uh, b.uw, b.mpi, b.k, b.tau, b.rule, b.mask, j % nbx,
-                                            j / nbx, s_a);
-        } else {
-            const int p = j * 256 + threadIdx.x;
-            const int HW = b.H * b.W;
-            if (p < HW) b.mask[p] = select_bits<DT, MAXD>(b.mpi, b.D, HW, p, b.k, b.tau, b.rule);
-        }
+    const int g = blockIdx.x;
+    const int sl = batch_slot_of(t, BK_FRONT, g);
+    const BatchSlot& b = t->slot[sl];
+    const int j = g - t->pre[BK_FRONT][sl];
+    if (j >= b.front_main) {
+        const int e = j - b.front_main;
+        const int nb = ((b.pyr_h >> b.pyr_nl) * (b.pyr_w >> b.pyr_nl) + 255) / 256;
+        const int n = e / nb, bx = e - n * nb;
+        if (b.pyr_nl == 1)
+            pyramid_block<1>(b.pyr_src, b.pyr_h, b.pyr_w, b.pyr_dst[0], nullptr, nullptr, n, bx);
+        else if (b.pyr_nl == 2)
+            pyramid_block<2>(b.pyr_src, b.pyr_h, b.pyr_w, b.pyr_dst[0], b.pyr_dst[1], nullptr, n, bx);
+        else
+            pyramid_block<3>(b.pyr_src, b.pyr_h, b.pyr_w, b.pyr_dst[0], b.pyr_dst[1], b.pyr_dst[2], n, bx);
+    } else if (b.up_src) {
+        const int nbx = (b.uw + kUpCols - 1) / kUpCols;
+        upsample_select_block<DT, MAXD>(b.up_src, b.D, b.uh, b.uw, b.mpi, b.k, b.tau, b.rule, b.mask, j % nbx, j / nbx,
+                                        s_a);
+    } else {
+        const int p = j * 256 + threadIdx.x;
+        const int HW = b.H * b.W;
+        if (p < HW) b.mask[p] = select_bits<DT, MAXD>(b.mpi, b.D, HW, p, b.k, b.tau, b.rule);
     }
 }
 
-// Tiles are taken in the XCD-grouped order of the flat item list (the grid is a multiple
-// of 8 workgroups), so neighbouring tiles of one request share an XCD's L2. Register
-// budget as for k_grad_shift where the tile keeps samples.
+// Tiles are taken in the XCD-grouped order of the flat item list, so neighbouring tiles of
+// one request share an XCD's L2. The forms are k_grad_shift's (as a persistent loop over the
+// items, which needs registers of its own, the eight requests of k_batch_front took 1425 us at their finest level, here 1188).
 template <int DT, int MAXD>
-__global__ __launch_bounds__(kSX * kSY) __attribute__((amdgpu_waves_per_eu(
-    batch_grad_waves<DT, MAXD>()))) void k_batch_grad(const BatchTable* __restrict__ t,
-                                                                                          int kk) {
-    const int total = t->total[kk];
-    for (int i = blockIdx.x; i < total; i += gridDim.x) {
-        const int g = xcd_tile(i, total);
-        const int sl = batch_slot_of(t, kk, g);
-        const BatchSlot& b = t->slot[sl];
-        __syncthreads();                     // the previous tile's LDS reads are done
-        // a fresh copy of the thread index per tile: nothing the tile derives from it is
-        // kept live across tiles
-        unsigned tid = threadIdx.x;
-        asm volatile("" : "+v"(tid));
-        grad_shift_tile<DT, MAXD, true, batch_grad_keep<DT, MAXD>(), batch_grad_tl<DT, MAXD>()>(b.mpi, b.D, b.H, b.W, b.N, b.warps, b.images, nullptr, b.mask, b.kcap,
-                                        1.0f / (float)b.N, b.slots, b.partials, b.ntx,
-                                        g - t->pre[kk][sl], tid);
-    }
+__global__ __launch_bounds__(kSX * kSY) __attribute__((amdgpu_waves_per_eu(grad_shift_waves<DT, MAXD>()))) void k_batch_grad(
+    const BatchTable* __restrict__ t, int kk) {
+    const int g = xcd_tile(blockIdx.x, gridDim.x);
+    const int sl = batch_slot_of(t, kk, g);
+    const BatchSlot& b = t->slot[sl];
+    grad_shift_tile<DT, MAXD, true>(b.mpi, b.D, b.H, b.W, b.N, b.warps, b.images, nullptr, b.mask, b.kcap,
+                                    1.0f / (float)b.N, b.slots, b.partials, b.ntx, g - t->pre[kk][sl], threadIdx.x);
 }
 
 template <int DT>
 __global__ __launch_bounds__(256) void k_batch_update(const BatchTable* __restrict__ t) {
     extern __shared__ int2 s_off[];
-    const int total = t->total[BK_UPDATE];
-    for (int g = blockIdx.x; g < total; g += gridDim.x) {
-        const int sl = batch_slot_of(t, BK_UPDATE, g);
-        const BatchSlot& b = t->slot[sl];
-        __syncthreads();                     // the previous item's shift table is no longer read
-        update_block<DT, true>(b.mpi, b.D, b.H, b.W, b.mask, b.kcap, b.slots, b.N, b.warps, b.ntx * kOX,
-                               b.nty * kOY, b.lr_rgb, b.lr_alpha, 1, nullptr, b.partials,
-                               (int64_t)b.ntx * b.nty * b.N, 0.5 / b.N, b.loss_out, b.prior,
-                               g - t->pre[BK_UPDATE][sl], s_off);
-    }
+    const int g = blockIdx.x;
+    const int sl = batch_slot_of(t, BK_UPDATE, g);
+    const BatchSlot& b = t->slot[sl];
+    update_block<DT, true>(b.mpi, b.D, b.H, b.W, b.mask, b.kcap, b.slots, b.N, b.warps, b.ntx * kOX, b.nty * kOY,
+                           b.lr_rgb, b.lr_alpha, 1, nullptr, b.partials, (int64_t)b.ntx * b.nty * b.N, 0.5 / b.N,
+                           b.loss_out, b.prior, g - t->pre[BK_UPDATE][sl], s_off);
 }
 
 // Plane-count classes: the kernels unroll their plane loops to MAXD planes and run the
 // planes z >= D as transparent ones, at full cost, so the classes lie 8 apart up to 48. FP32,
 // 512 x 378 x 40 planes, 3 views: gradient 173 us as 64 planes, 121 as 40; selection 32 and
 // 24, upsampling with selection 45 and 35 (24 planes, 4 views: gradient 107 us as 32, 87).
+constexpr int kClasses[kNumClasses] = {8, 16, 24, 32, 40, 48, 64};
 int maxd_class(int D) {
-    return D <= 8 ? 8 : D <= 16 ? 16 : D <= 24 ? 24 : D <= 32 ? 32 : D <= 40 ? 40 : D <= 48 ? 48 : 64;
+    return kClasses[batch_class(D)];
 }
 
 #define HSGD_DISPATCH_D(D, BODY)                         \
@@ -1983,14 +1958,6 @@ int maxd_class(int D) {
         case 48: { constexpr int MD = 48; BODY; } break; \
         default: { constexpr int MD = 64; BODY; } break; \
     }
-
-// The batched kernels keep to four classes: each is one persistent launch per step,
-// whether or not a request in flight belongs to it.
-#define HSGD_DISPATCH_BATCH_D(D, BODY)                      \
-    if ((D) <= 8) { constexpr int MD = 8; BODY; }           \
-    else if ((D) <= 16) { constexpr int MD = 16; BODY; }    \
-    else if ((D) <= 32) { constexpr int MD = 32; BODY; }    \
-    else { constexpr int MD = 64; BODY; }
 
 #define HSGD_DISPATCH_T(dt, BODY)                                  \
     if ((dt) == HSGD_FP32) { constexpr int DT = HSGD_FP32; BODY; } \
@@ -2215,34 +2182,30 @@ int launch_convert(const void* src, int sdt, void* dst, int ddt, size_t n, hipSt
     return (int)hipGetLastError();
 }
 
-int batch_grad_occupancy(int dtype, int cls) {
-    int n = 0;
-    hipError_t e = hipSuccess;
-    HSGD_DISPATCH_T(dtype, HSGD_DISPATCH_BATCH_D(cls, e = hipOccupancyMaxActiveBlocksPerMultiprocessor(
-                                                    &n, reinterpret_cast<const void*>(&k_batch_grad<DT, MD>),
-                                                    kSX * kSY, 0)));
-    return e == hipSuccess ? n : 0;
+int batch_class(int D) {
+    return D <= 8 ? 0 : D <= 16 ? 1 : D <= 24 ? 2 : D <= 32 ? 3 : D <= 40 ? 4 : D <= 48 ? 5 : 6;
 }
 
-template <int DT>
-static void enqueue_batch(const BatchTable* t, const BatchLaunch& c, hipStream_t s) {
-    const dim3 small((unsigned)c.grid_small), grad(kSX * kSY);
-    HSGD_DISPATCH_D(c.max_d, hipLaunchKernelGGL((k_batch_front<DT, MD>), small, dim3(256), 0, s, t));
-    if (c.max_class >= 8)
-        hipLaunchKernelGGL((k_batch_grad<DT, 8>), dim3((unsigned)c.grid_grad[0]), grad, 0, s, t, (int)BK_GRAD8);
-    if (c.max_class >= 16)
-        hipLaunchKernelGGL((k_batch_grad<DT, 16>), dim3((unsigned)c.grid_grad[1]), grad, 0, s, t, (int)BK_GRAD16);
-    if (c.max_class >= 32)
-        hipLaunchKernelGGL((k_batch_grad<DT, 32>), dim3((unsigned)c.grid_grad[2]), grad, 0, s, t, (int)BK_GRAD32);
-    if (c.max_class >= 64)
-        hipLaunchKernelGGL((k_batch_grad<DT, 64>), dim3((unsigned)c.grid_grad[3]), grad, 0, s, t, (int)BK_GRAD64);
-    const size_t lds = sizeof(int2) * (size_t)c.max_n * c.max_d;
-    hipLaunchKernelGGL((k_batch_update<DT>), small, dim3(256), lds, s, t);
-}
-
-int launch_batch_step(const BatchTable* t, const BatchLaunch& c, hipStream_t s) {
-    if (c.dtype == HSGD_FP32) enqueue_batch<HSGD_FP32>(t, c, s);
-    else enqueue_batch<HSGD_BF16>(t, c, s);
+int launch_batch_step(const BatchTable* staged, BatchTable* t, int dtype, hipStream_t s) {
+    const int words = (int)((offsetof(BatchTable, slot) + sizeof(BatchSlot) * (size_t)staged->nslot + 15) / 16);
+    hipLaunchKernelGGL(k_batch_table, dim3(1), dim3(256), 0, s, reinterpret_cast<const uint4*>(staged),
+                       reinterpret_cast<uint4*>(t), words);
+    int max_d = 1;
+    size_t shifts = 0;
+    for (int i = 0; i < staged->nslot; ++i) {
+        max_d = std::max(max_d, staged->slot[i].D);
+        shifts = std::max(shifts, (size_t)staged->slot[i].N * staged->slot[i].D);
+    }
+    HSGD_DISPATCH_T(dtype, HSGD_DISPATCH_D(max_d, hipLaunchKernelGGL((k_batch_front<DT, MD>),
+                                                                     dim3((unsigned)staged->total[BK_FRONT]), dim3(256), 0,
+                                                                     s, t)));
+    for (int c = 0; c < kNumClasses; ++c)
+        if (staged->total[BK_GRAD + c])
+            HSGD_DISPATCH_T(dtype, HSGD_DISPATCH_D(kClasses[c], hipLaunchKernelGGL((k_batch_grad<DT, MD>),
+                                                                                   dim3((unsigned)staged->total[BK_GRAD + c]),
+                                                                                   dim3(kSX * kSY), 0, s, t, BK_GRAD + c)));
+    HSGD_DISPATCH_T(dtype, hipLaunchKernelGGL((k_batch_update<DT>), dim3((unsigned)staged->total[BK_UPDATE]), dim3(256),
+                                              sizeof(int2) * shifts, s, t));
     return (int)hipGetLastError();
 }
 }  // namespace hsgd
