@@ -875,10 +875,14 @@ __device__ __forceinline__ float rlf(float v, int lane) {
 // of the own column, then the horizontal lerp with the next lane's (4 instructions, the
 // lane shift folded into a multiply). wt = (upper row weight, lower row weight, 1 - fx,
 // fx), a row outside the plane weighted 0.
-__device__ __forceinline__ float lerp_taps(float a0, float a1, const float4& wt) {
+template <typename W>
+__device__ __forceinline__ float lerp_taps(float a0, float a1, const W& wt) {
     const float v = __builtin_fmaf(a1, wt.y, a0 * wt.x);
     return __builtin_fmaf(v, wt.z, lane_from_next(v) * wt.w);
 }
+
+using f32x4 = float __attribute__((ext_vector_type(4)));
+using lds_f32x4 = __attribute__((address_space(3))) f32x4;
 
 // One 64 x 8 tile of one view (tile = view + N * (tx + ntx * ty)); every thread of the
 // workgroup calls it.
@@ -890,8 +894,13 @@ __device__ __forceinline__ float lerp_taps(float a0, float a1, const float4& wt)
 // SIMD hold without spills once 2 workgroups' 160 KB of LDS are filled with transmittances.
 // The forms are within a few percent of each other (BF16, 24 planes, 512 x 384, 4 views:
 // 85 us against 88 at 6 waves; 48 planes: 172 us against 179 without kept samples): the
-// kernel is bound by its vector instructions, some 130 per wave and plane and scan pair, so
-// what counts is to run no more planes than the MPI has (see maxd_class).
+// kernel is bound by issuing its vector instructions, 105 per wave, plane and pair of scans
+// (BF16; 62 of them the interpolation, the compositing and the adjoint), so what counts is to
+// run no more planes than the MPI has (see maxd_class) and no more instructions per plane.
+// With separate weight tables for every row, the shift's fractions beside them and LDS
+// addresses rebuilt per plane it was 119: FP32, 512 x 384 x 32, 4 views 119 us, now 108 (46 and
+// 23 us one and two levels below, from 51 and 26); BF16, 1920 x 1080 x 64, 8 views 4442 us, now
+// 4343.
 template <int DT, int MAXD>
 constexpr int grad_shift_keep() {
     if (MAXD <= 16 || (DT == HSGD_BF16 && MAXD == 32)) return 0;
@@ -915,11 +924,12 @@ __device__ __forceinline__ void grad_shift_tile(
     const float* __restrict__ images, const float* __restrict__ dimg, const uint64_t* __restrict__ mask,
     int kcap, float inv_n, float4* __restrict__ slots, float* __restrict__ partials, int ntx, int tile,
     unsigned tid) {
-    __shared__ float4 s_h[2][kSX * kSY];
+    // horizontal halves, two buffers of the tile (one wave row of padding in front, so that
+    // the row above is at a constant distance below for every wave)
+    __shared__ f32x4 s_h[kSX + 2 * kSX * kSY];
     __shared__ uint64_t s_bits[kSY];
     __shared__ float sred[kSX * kSY / 64];
-    __shared__ float4 s_w[kSY][MAXD];                       // per wave row and plane: tap weights
-    __shared__ float2 s_f[MAXD];                            // per plane: the shift's fraction
+    __shared__ f32x4 s_w[MAXD];                             // per plane: tap weights
     __shared__ uint32_t s_code[(MAXD + 3) / 4][kSX * kSY];  // rank bytes of 4 planes per thread
     // Transmittance in front of the first kTL planes: these live longest (from the start of
     // the front-to-back scan to the end of the back-to-front one), so they go to LDS instead
@@ -937,7 +947,6 @@ __device__ __forceinline__ void grad_shift_tile(
     const bool ray = lane < kSX - 1 && (unsigned)x < (unsigned)W && (unsigned)y < (unsigned)H;
     const bool owner = lane >= 1 && lane < kSX - 1 && wv >= 1;
     const int HW = H * W;
-    const uint64_t full = plane_bits(D);
 
     // Plane tables, one entry per lane z < MAXD (read per plane with v_readlane, feeding
     // scalar address arithmetic):
@@ -946,16 +955,14 @@ __device__ __forceinline__ void grad_shift_tile(
     //         | 4 if the row below is the plane's first row (the upper one lies above it);
     //   lcol  the integer column shift times the voxel size (ix * s).
     // A wave's tap columns are then x + ix for its lanes' x.
-    // The bilinear weights of each plane for this wave's row (lerp_taps' four; a tap row
-    // outside the plane weighted 0) and the shift's fraction go to LDS, read per plane as
-    // broadcasts. Planes z >= D repeat plane D - 1 with zero weights.
+    // The bilinear weights of each plane (lerp_taps' four; the adjoint's as well) go to LDS,
+    // read per plane as broadcasts: a tap outside the plane reads 0, so they hold for every
+    // row. Planes z >= D repeat plane D - 1 with zero weights.
     constexpr int S = Vox<DT>::kBytes;
     const int rowbytes = W * S;
     const int dlast = __builtin_amdgcn_readfirstlane(D - 1);    // last plane, wave-uniform
     int lrow = 0, lcol = 0;
     if (lane < MAXD) {
-        float4 wt = make_float4(0.f, 0.f, 0.f, 0.f);
-        float2 fr = make_float2(0.f, 0.f);
         const hsgd_warp& w = warps[(size_t)view * D + min(lane, dlast)];
         const int Y0 = y + w.iy;
         const bool in0 = (unsigned)Y0 < (unsigned)H, in1 = (unsigned)(Y0 + 1) < (unsigned)H;
@@ -963,13 +970,15 @@ __device__ __forceinline__ void grad_shift_tile(
         // (a shift beyond the frame and its halo only ever reads padding; clamping it there
         // keeps every lane's byte offset from wrapping into the row)
         lcol = min(max(w.ix, -(W + 64)), W + 64) * S;
-        if (lane < D) {
-            fr = make_float2(w.fx, w.fy);
-            wt = make_float4(in0 ? 1.0f - fr.y : 0.0f, in1 ? fr.y : 0.0f, 1.0f - fr.x, fr.x);
-        }
-        s_w[wv][lane] = wt;
-        if (wv == 0) s_f[lane] = fr;
+        const f32x4 none = {0.0f, 0.0f, 0.0f, 0.0f};
+        const f32x4 wt = {1.0f - w.fy, w.fy, 1.0f - w.fx, w.fx};
+        if (wv == 0) s_w[lane] = lane < D ? wt : none;
     }
+    // (the LDS addresses read per plane stay in registers: rebuilt from constants, as the
+    // compiler would, they cost vector instructions, which bound this kernel)
+    lds_f32x4* wts = (lds_f32x4*)s_w;
+    lds_f32x4* halves = (lds_f32x4*)s_h + tid;              // the row above's; the own row's is kSX further
+    asm volatile("" : "+v"(wts), "+v"(halves));
     const unsigned xs = (unsigned)x * (unsigned)S;                // wraps when x < 0: outside
     __syncthreads();
 
@@ -1008,14 +1017,13 @@ __device__ __forceinline__ void grad_shift_tile(
     // column), through a buffer resource over the cell's mask row: a cell outside the
     // plane reads 0, i.e. unselected
     auto fetch_mask = [&](const Taps2& f) -> uint64_t {
-        if (!MASKED) return full;
+        if (!MASKED) return 0;
         const char* row = reinterpret_cast<const char*>(mask) + (f.row & ~7u) / (unsigned)(S / 8);
         const auto v = __builtin_amdgcn_raw_buffer_load_b64(row_rsrc(row, (f.row & 1u) ? W * 8 : 0),
                                                             f.off(xs) / (unsigned)(S / 8), 0, 0);
         return ((uint64_t)v[1] << 32) | v[0];
     };
-    auto sample = [&](int z, const Taps2& f) {
-        const float4 wt = s_w[wv][z];
+    auto sample = [&](const f32x4& wt, const Taps2& f) {
         const float4 a0 = Vox<DT>::decode(f.t00), a1 = Vox<DT>::decode(f.t01);
         float4 s;
         s.x = lerp_taps(a0.x, a1.x, wt);
@@ -1053,15 +1061,16 @@ __device__ __forceinline__ void grad_shift_tile(
             }
 #pragma unroll
         for (int z = 0; z < MAXD; ++z) {
-            asm volatile("" : "+v"(go));
-            if (!__builtin_amdgcn_readfirstlane(go)) break;
+            asm volatile("" : "+s"(go));
+            if (!go) break;
             const Taps2 cur = q[z % kAhead];
             const uint64_t m = qm[z % kAhead];
             if (z + kAhead < MAXD) {
                 q[z % kAhead] = fetch(z + kAhead, HW);
                 qm[z % kAhead] = fetch_mask(q[z % kAhead]);
             }
-            const float4 s = sample(z, cur);
+            const f32x4 wt = wts[z];
+            const float4 s = sample(wt, cur);
             if (kKeep > 0 && z >= MAXD - kKeep) Sk[z >= MAXD - kKeep ? z - (MAXD - kKeep) : 0] = s;
             if (z < kTL)
                 s_T[z < kTL ? z : 0][tid] = T;
@@ -1072,18 +1081,26 @@ __device__ __forceinline__ void grad_shift_tile(
             c1 = __builtin_fmaf(wgt, s.y, c1);
             c2 = __builtin_fmaf(wgt, s.z, c2);
             T *= 1.0f - s.w;
-            // (a cell outside the plane has a zero mask word; without a mask, check the range)
-            const bool cell = owner && z < D && (MASKED || ((cur.row & 1u) && cur.off(xs) < (unsigned)rowbytes));
-            // branch-free: rank + 1 of the owned cell's plane z if selected, else 0
-            const uint32_t sel = cell ? (uint32_t)((m >> z) & 1) : 0u;
-            const uint32_t rank = (uint32_t)__popcll(m & ((1ull << z) - 1));
-            const uint32_t rc = (sel && rank < (uint32_t)kcap) ? rank + 1 : 0u;
-            code |= rc << ((z & 3) * 8);
+            // branch-free: n = rank + 1 of the owned cell's plane z if selected, else 0. With the
+            // mask shifted so that bit z is the sign, the bits left count rank + 1. (A cell
+            // outside the plane has a zero mask word; without a mask, check the range.)
+            bool sel = owner && z < D;
+            uint32_t n = z + 1;
+            if (MASKED) {
+                const uint32_t lo = (uint32_t)m, hi = (uint32_t)(m >> 32);
+                const uint32_t t = z < 32 ? lo << (31 - z) : hi << (63 - z);
+                n = __popc(t) + (z < 32 ? 0 : __popc(lo));
+                sel = sel && (int)t < 0;
+            } else {
+                sel = sel && (cur.row & 1u) && cur.off(xs) < (unsigned)rowbytes;
+            }
+            sel = sel && n <= (uint32_t)kcap;
+            code |= (sel ? n : 0u) << ((z & 3) * 8);
             if ((z & 3) == 3 || z == MAXD - 1) {
                 s_code[z >> 2][tid] = code;
                 code = 0;
             }
-            if (__ballot(rc != 0)) own_bits |= 1ull << z;
+            if (__builtin_amdgcn_ballot_w64(sel)) own_bits |= 1ull << z;
             __builtin_amdgcn_sched_barrier(0);
         }
         // The look-ahead loads are consumed on the path out of the loop as well, so that
@@ -1139,10 +1156,11 @@ __device__ __forceinline__ void grad_shift_tile(
 #pragma unroll
         for (int zz = 0; zz < MAXD; ++zz) {
             const int z = MAXD - 1 - zz;
-            asm volatile("" : "+v"(go));
-            if (!__builtin_amdgcn_readfirstlane(go)) break;
+            asm volatile("" : "+s"(go));
+            if (!go) break;
             Taps2 cur;
             float4 s;
+            const f32x4 wt = wts[z];
             if (zz < kKeep) {
                 cur.row = (unsigned)rl(lrow, z);
                 cur.col = (unsigned)rl(lcol, z);
@@ -1151,12 +1169,11 @@ __device__ __forceinline__ void grad_shift_tile(
                 const int zk = zz - kKeep;
                 cur = q[zk % kAhead];
                 if (zz + kAhead < MAXD) q[zk % kAhead] = fetch(z - kAhead, HW2);
-                s = sample(z, cur);
+                s = sample(wt, cur);
             }
-            const float2 fr = s_f[z];
-            const float fx = fr.x, fy = fr.y;
             if ((z & 3) == 3 || z == MAXD - 1) rcode = s_code[z >> 2][tid];
-            float4* buf = s_h[z & 1];
+            lds_f32x4* const up = halves + (z & 1) * (kSX * kSY);
+            lds_f32x4* const own = up + kSX;
             // the colour of plane z against the composite behind it: the alpha adjoint's
             // factor and the step of the behind composite, B <- B + a (c - B)
             const float d0 = s.x - b0, d1 = s.y - b1, d2 = s.z - b2;
@@ -1170,13 +1187,13 @@ __device__ __forceinline__ void grad_shift_tile(
                 a.w = Tz * __builtin_fmaf(g2, d2, __builtin_fmaf(g1, d1, g0 * d0));
                 // horizontal half of the transposed bilinear: this ray (1 - fx) and the
                 // ray to the left (fx) both touch the owned cell's row
-                const float gx = 1.0f - fx;
-                float4 h;
+                const float gx = wt.z, fx = wt.w;
+                f32x4 h;
                 h.x = __builtin_fmaf(a.x, gx, lane_from_prev(a.x) * fx);
                 h.y = __builtin_fmaf(a.y, gx, lane_from_prev(a.y) * fx);
                 h.z = __builtin_fmaf(a.z, gx, lane_from_prev(a.z) * fx);
                 h.w = __builtin_fmaf(a.w, gx, lane_from_prev(a.w) * fx);
-                buf[tid] = h;
+                *own = h;
             }
             b0 = __builtin_fmaf(s.w, d0, b0);
             b1 = __builtin_fmaf(s.w, d1, b1);
@@ -1187,9 +1204,8 @@ __device__ __forceinline__ void grad_shift_tile(
                 if (rc) {
                     // this row's and the row above's horizontal halves, both from LDS (the
                     // own half is not kept in registers across the barrier)
-                    const float4 h = buf[tid];
-                    const float4 hu = buf[tid - 64];
-                    const float gy = 1.0f - fy;
+                    const f32x4 h = *own, hu = *up;
+                    const float gy = wt.x, fy = wt.y;
                     float4 c;
                     c.x = __builtin_fmaf(hu.x, fy, h.x * gy);
                     c.y = __builtin_fmaf(hu.y, fy, h.y * gy);
