@@ -2175,7 +2175,9 @@ int launch_grad_step(const hsgd_mpi& m, const hsgd_views& v, const uint64_t* mas
     const bool shift = (v.flags & HSGD_VIEWS_SHIFT_ONLY) != 0;
     int64_t nparts;
     int cover_w = 0, cover_h = 0;
-    if (grad_out) {
+    // (without a mask every entry is selected, and the update writes them all: 8 us of 50 for
+    // 256 x 192 x 16, 3 views)
+    if (grad_out && mask) {
         ProfScope ps(HSGD_K_FILL, s);
         const int64_t n = (int64_t)m.D * HW;
         hipLaunchKernelGGL(k_fill_zero, dim3((unsigned)std::min<int64_t>(ceil_div(n, 256), 8192)), dim3(256), 0, s,
