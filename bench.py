@@ -233,7 +233,7 @@ def serving_bench(args):
         "config": {
             "workload": ("continuous batching, 8 persistent scenes (3x 256x192x16 k2, 3x 512x384x32 k4, "
                          "2x 1008x756x32 k4; 3-5 views; 3 levels, 1 iteration each), BF16 MPIs resident, "
-                         "one hipGraph launch per batched iteration, 8 slots"),
+                         "one launch per kernel and batched iteration, 8 slots"),
             "arrival_rate_per_s": args.rate,
         },
         "p50_ms": open_loop["p50_ms"],

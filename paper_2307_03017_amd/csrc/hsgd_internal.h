@@ -13,7 +13,7 @@ constexpr int kMaxD = 64;
 constexpr int kMaxN = 64;
 constexpr size_t kAlign = 256;
 
-// Tile of one render/gradient workgroup: a 64-wide row per wave, 4 waves.
+// Tile of one general-warp render workgroup: a 64-wide row per wave, 4 waves.
 constexpr int kTileW = 64;
 constexpr int kTileH = 4;
 constexpr int kBlock = kTileW * kTileH;

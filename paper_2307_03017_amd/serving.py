@@ -6,7 +6,7 @@ fine in BF16 storage. Requests arrive open-loop (Poisson). The loop admits queue
 requests first-come first-served whenever the core has a free slot and HBM budget,
 evicting idle streams (least recently used) when a new stream does not fit, runs one
 batched iteration (hsgd_batch_step: every request in flight advances one level-iteration,
-all in one captured HIP graph) and collects completions. Latency is arrival (host clock)
+all in the same launches) and collects completions. Latency is arrival (host clock)
 to the completion of the request's last iteration on the device (its step event, mapped
 onto the host clock through the batch's reference event).
 
