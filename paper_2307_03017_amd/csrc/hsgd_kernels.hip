@@ -2043,7 +2043,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(DT == HSGD_
 
 // Tiles are taken in the XCD-grouped order of the flat item list, so neighbouring tiles of
 // one request share an XCD's L2. The forms are k_grad_shift's (as a persistent loop over the
-// items, which needs registers of its own, the eight requests of k_batch_front took 1425 us at their finest level, here 1188).
+// items, which needs registers of its own, the eight requests of k_batch_front took 1425 us at their finest level, here 1188; now 1165).
 template <int DT, int MAXD>
 __global__ __launch_bounds__(kSX * kSY) __attribute__((amdgpu_waves_per_eu(grad_shift_waves<DT, MAXD>()))) void k_batch_grad(
     const BatchTable* __restrict__ t, int kk) {
