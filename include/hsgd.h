@@ -382,9 +382,9 @@ hsgd_status hsgd_batch_destroy(hsgd_batch* b);
 hsgd_status hsgd_batch_admit(hsgd_batch* b, const hsgd_request* r, int64_t* ticket);
 
 /* Enqueues one iteration of every admitted request on stream (one table upload, one
- * launch per kernel with work). Blocks the host only while the fourth step before it still runs (which
- * holds its staging buffer). Steps run in the order they are enqueued whatever streams they are
- * given: a step enqueued on a stream other than the previous step's first makes that
+ * launch per kernel with work). Blocks the host only while the fourth step before it still
+ * runs (which holds its staging buffer). Steps run in the order they are enqueued whatever
+ * streams they are given: a step enqueued on a stream other than the previous step's first makes that
  * stream wait for the previous step to complete (all steps share one device table, and
  * each continues the requests of the one before). Outputs (each may be NULL): *n_active requests stepped; the tickets
  * of requests whose last iteration this step holds, up to max_finished of them, and their

@@ -5,7 +5,9 @@
 //               (Sec. 3.3 Gradient Sparsification, Eq. gradient / Eq. overA)
 //  k_scan_*     exclusive scan of those counts in plane-major order
 //  k_compact    wavefront ballot/popcount compaction -> ascending linear ids (S)
-//  k_render     warp + front-to-back over per view ray (Eq. render, Eq. over, Eq. homo)
+//  k_render     warp + front-to-back over per view ray (Eq. render, Eq. over, Eq. homo);
+//               k_render_shift and k_render_shift_rows for translations (one row of rays
+//               per wave on small calls, four or eight on large ones)
 //  k_grad       forward scan, residual, back-to-front adjoint scan, transposed bilinear
 //               scatter restricted to S (Sec. 3.3; Eq. 4 gradient)
 //  k_update     restore the sparse step onto S with clamp (the M_{n+1} update)
@@ -1984,7 +1986,7 @@ __global__ __launch_bounds__(256) void k_convert(const void* __restrict__ src, v
 }
 
 // ------------------------------------------------------------------------------------
-// batched serving step: persistent kernels over the work items of every in-flight request
+// batched serving step: kernels over the work items of every in-flight request
 // ------------------------------------------------------------------------------------
 // Each kernel is launched over exactly its items of the step: workgroup g takes item g of
 // the list concatenated over the requests.
