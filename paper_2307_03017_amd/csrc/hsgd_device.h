@@ -39,11 +39,48 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t row_rsrc(const char* row, int 
 struct RowMap {
     double a0, a1, a2, b0, b1, b2;
 };
-__device__ __forceinline__ RowMap row_map(const hsgd_warp& w, int y) {
-    const double yd = (double)y;
-    if (w.is_shift) return RowMap{1.0, 0.0, 0.0, (double)w.ix + (double)w.fx, yd + (double)w.iy + (double)w.fy, 1.0};
-    return RowMap{w.G[0], w.G[3], w.G[6], __builtin_fma(w.G[1], yd, w.G[2]), __builtin_fma(w.G[4], yd, w.G[5]),
-                  __builtin_fma(w.G[7], yd, w.G[8])};
+__device__ __forceinline__ RowMap row_map(const double* g, double yd) {
+    return RowMap{g[0], g[3], g[6], __builtin_fma(g[1], yd, g[2]), __builtin_fma(g[4], yd, g[5]),
+                  __builtin_fma(g[7], yd, g[8])};
+}
+__device__ __forceinline__ RowMap shift_row(const hsgd_warp& w, double yd) {
+    return RowMap{1.0, 0.0, 0.0, (double)w.ix + (double)w.fx, yd + (double)w.iy + (double)w.fy, 1.0};
+}
+
+// The map of a record as the kernels that tabulate maps use it: they compute positions without
+// a check, so what these cannot be computed from is replaced here, once per plane, by a map
+// that places every pixel where the numbers would. An entry of the first two rows that is no
+// number or infinite (from 2^960 on it counts as that), a third row with such an entry that is
+// not +inf, or one of no normal number, places none in front. A third row with a +inf has an
+// infinite q2, that is the position (0, 0), except where the inf is multiplied by x = 0 or
+// y = 0; two infs so multiplied place none. (A check of each position cost the gradient 1 to 3%.)
+struct PlaneMap {
+    double g[9];
+};
+__device__ __forceinline__ PlaneMap plane_map(const hsgd_warp& w) {
+    PlaneMap m;
+    if (w.is_shift) {
+        const RowMap r = shift_row(w, 0.0);
+        return PlaneMap{{1.0, 0.0, r.b0, 0.0, 1.0, r.b1, 0.0, 0.0, 1.0}};
+    }
+    constexpr int kHuge = 1023 + 960;
+    int e[9], most = 0;                                     // biased exponents
+    for (int i = 0; i < 9; ++i) {
+        m.g[i] = w.G[i];
+        e[i] = (int)((__builtin_bit_cast(uint64_t, m.g[i]) >> 52) & 0x7ffu);
+        most = max(most, e[i]);
+    }
+    if (most >= kHuge || (e[6] | e[7] | e[8]) == 0) {
+        constexpr double kFar = 0x1p900;
+        const bool ix = e[6] >= kHuge, iy = e[7] >= kHuge;
+        bool none = (ix && iy) || !(ix || iy || e[8] >= kHuge);
+        for (int i = 0; i < 9; ++i) none = none || (e[i] >= kHuge && (i < 6 || !(m.g[i] > 0.0)));
+        for (int i = 0; i < 6; ++i) m.g[i] = none ? 0.0 : m.g[i];
+        m.g[6] = !none && ix ? kFar : 0.0;
+        m.g[7] = !none && iy ? kFar : 0.0;
+        m.g[8] = !none && !ix && !iy ? kFar : -1.0;
+    }
+    return m;
 }
 
 // 1 / q to FP64 accuracy: the hardware's estimate and two Newton steps (its ~24 correct bits
@@ -61,16 +98,27 @@ struct MapPos {
     float fx, fy;
     bool front;
 };
+// CHECK: of any map; otherwise of a plane_map.
+template <bool CHECK>
 __device__ __forceinline__ MapPos map_pos(const RowMap& m, double x) {
+    const double q0 = __builtin_fma(m.a0, x, m.b0), q1 = __builtin_fma(m.a1, x, m.b1);
     const double q2 = __builtin_fma(m.a2, x, m.b2);
-    const double r = rcp_f64(q2);
-    const double u = __builtin_fma(m.a0, x, m.b0) * r, v = __builtin_fma(m.a1, x, m.b1) * r;
+    double r = rcp_f64(q2);
+    double u = q0 * r, v = q1 * r;
     MapPos p;
+    p.front = q2 > 0.0;
+    // No number: from such an entry, or a q2 that the Newton steps do not bear (infinite, or so
+    // small that its reciprocal is). The division decides; what is no number then is outside.
+    if (CHECK && __builtin_amdgcn_ballot_w64(__builtin_isunordered(u, v))) {
+        r = 1.0 / q2;
+        u = q0 * r;
+        v = q1 * r;
+        p.front = p.front && !__builtin_isunordered(u, v);
+    }
     p.fu = floor(u);
     p.fv = floor(v);
     p.fx = (float)(u - p.fu);
     p.fy = (float)(v - p.fv);
-    p.front = q2 > 0.0;
     return p;
 }
 

@@ -421,7 +421,9 @@ __global__ __launch_bounds__(kBlock) void k_render(const void* __restrict__ mpi,
     const int x0 = (t2 % ntx) * kTileW, y0 = (t2 / ntx) * kTileH;
     for (int i = threadIdx.x; i < kTileH * D; i += kBlock) {
         const int r = i / D, z = i - r * D;
-        s_map[r][z] = row_map(warps[(size_t)view * D + z], y0 + r);
+        const hsgd_warp& w = warps[(size_t)view * D + z];
+        const double yd = (double)(y0 + r);
+        s_map[r][z] = w.is_shift ? shift_row(w, yd) : row_map(plane_map(w).g, yd);
     }
     __syncthreads();
     const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
@@ -433,7 +435,7 @@ __global__ __launch_bounds__(kBlock) void k_render(const void* __restrict__ mpi,
         float fx, fy;
     };
     auto fetch = [&](int z) {
-        MapPos p = map_pos(s_map[wv][z], xd);
+        MapPos p = map_pos<false>(s_map[wv][z], xd);
         const TapOffs o = tap_offsets<S>(p, W, H);
         const auto rs = row_rsrc(reinterpret_cast<const char*>(mpi) + (size_t)z * plane_bytes, (int)plane_bytes);
         return Fetched{load_taps<DT>(rs, o), p.fx, p.fy};
@@ -648,21 +650,9 @@ __global__ __launch_bounds__(kGenThreads) __attribute__((amdgpu_waves_per_eu(4))
     const int x = (t2 % ntx) * kGenOX + lane, y = (t2 / ntx) * kGenY + wv;
     const int HW = H * W, D2 = (D + 1) & ~1;
     for (int z = tid; z < D2; z += kGenThreads) {
-        double g[9] = {0, 0, 0, 0, 0, 0, 0, 0, -1.0};       // planes behind the last: nowhere in front
-        if (z < D) {
-            const hsgd_warp& w = warps[(size_t)view * D + z];
-            const RowMap m0 = row_map(w, 0);
-            g[0] = m0.a0;
-            g[1] = w.is_shift ? 0.0 : w.G[1];
-            g[2] = m0.b0;
-            g[3] = m0.a1;
-            g[4] = w.is_shift ? 1.0 : w.G[4];
-            g[5] = m0.b1;
-            g[6] = m0.a2;
-            g[7] = w.is_shift ? 0.0 : w.G[7];
-            g[8] = m0.b2;
-        }
-        for (int i = 0; i < 9; ++i) s_map[z][i] = g[i];
+        PlaneMap m{{0, 0, 0, 0, 0, 0, 0, 0, -1.0}};          // planes behind the last: nowhere in front
+        if (z < D) m = plane_map(warps[(size_t)view * D + z]);
+        for (int i = 0; i < 9; ++i) s_map[z][i] = m.g[i];
     }
     __syncthreads();
     // rays that contribute; the other lanes sample like the rest and carry a zero residual
@@ -674,9 +664,7 @@ __global__ __launch_bounds__(kGenThreads) __attribute__((amdgpu_waves_per_eu(4))
         float fx, fy;
     };
     auto fetch = [&](int z, TapOffs& o, TapCell& c) {
-        const double* g = s_map[z];
-        MapPos p = map_pos(RowMap{g[0], g[3], g[6], __builtin_fma(g[1], yd, g[2]), __builtin_fma(g[4], yd, g[5]),
-                                  __builtin_fma(g[7], yd, g[8])}, xd);
+        MapPos p = map_pos<false>(row_map(s_map[z], yd), xd);
         o = tap_offsets<S>(p, W, H, c);
         return Fetched{load_taps<DT>(row_rsrc(reinterpret_cast<const char*>(mpi) + (size_t)min(z, D - 1) * plane_bytes,
                                               (int)plane_bytes), o), p.fx, p.fy};

@@ -139,12 +139,17 @@ __device__ __forceinline__ float3 psv_tap(__amdgpu_buffer_rsrc_t rs, unsigned of
     return make_float3(__uint_as_float(v[0]), __uint_as_float(v[1]), __uint_as_float(v[2]));
 }
 
+__device__ __forceinline__ RowMap psv_row(const hsgd_warp& w, int y) {
+    return w.is_shift ? shift_row(w, (double)y) : row_map(w.G, (double)y);
+}
+
 // The samples of a tile under a general map, straight to level 0 in LDS: a wave takes one row
 // of 64 pixels at a time (rows wv, wv + 4, ...), so that the lanes of a tap load read
 // neighbouring pixels. Four consecutive pixels per lane, as the translation path has them,
 // spread each load over 24 cache lines instead of 6-7 (1008x756, 32 planes, 5 views, 3
 // levels, BF16 volume: 622 us a launch that way with an IEEE division per position, 511 us
-// this way with the cheaper positions).
+// this way with the cheaper positions). A tile has four positions per lane, so they are checked
+// one by one (free here; checking the map first as plane_map does cost 2 to 3%).
 __device__ __forceinline__ void psv_sample_general(const float* __restrict__ im, const hsgd_warp& wp, int tx, int ty,
                                                    int H, int W, float* __restrict__ s_lv, int t) {
     const int lane = t & 63, wv = __builtin_amdgcn_readfirstlane(t >> 6);
@@ -153,13 +158,13 @@ __device__ __forceinline__ void psv_sample_general(const float* __restrict__ im,
     // the rows' parts of the map, by lanes 0..3 through LDS (only this wave reads them)
     __shared__ double s_row[4][4][3];
     if (lane < 4) {
-        const RowMap m = row_map(wp, ty * kPsvTH + 4 * lane + wv);
+        const RowMap m = psv_row(wp, ty * kPsvTH + 4 * lane + wv);
         s_row[wv][lane][0] = m.b0;
         s_row[wv][lane][1] = m.b1;
         s_row[wv][lane][2] = m.b2;
     }
     __builtin_amdgcn_wave_barrier();
-    RowMap m = row_map(wp, 0);                              // its a0, a1, a2
+    RowMap m = psv_row(wp, 0);                              // its a0, a1, a2
     MapPos p[4];
     float3 a[4], b[4], c[4], d[4];
 #pragma unroll
@@ -167,7 +172,7 @@ __device__ __forceinline__ void psv_sample_general(const float* __restrict__ im,
         m.b0 = s_row[wv][j][0];
         m.b1 = s_row[wv][j][1];
         m.b2 = s_row[wv][j][2];
-        p[j] = map_pos(m, x);
+        p[j] = map_pos<true>(m, x);
         const TapOffs o = tap_offsets<12>(p[j], W, H);
         a[j] = psv_tap(rs, o.o00);
         b[j] = psv_tap(rs, o.o10);

@@ -1,0 +1,79 @@
+"""Values that are no numbers, in maps and planes of the general kernels: what the zero padding
+and the ray's frame exclude stays excluded, whatever the excluded numbers are.
+
+Bounds as for finite maps: a composite of D planes 10 (D + 2) 2^-24, a gradient entry 4 times
+that and 2^-24 per view and tap summed, relative to the largest entry.
+"""
+
+import numpy as np
+import pytest
+import torch
+
+from oracle import hsgd_oracle as O
+from paper_2307_03017_amd import hsgd
+from tests._problems import f32, mask_bits, rig
+
+pytestmark = pytest.mark.gpu
+
+EPS = 2.0 ** -24
+N, D, W, H = 2, 3, 70, 20
+
+
+def dev(x, dtype=torch.float32):
+    return torch.from_numpy(np.ascontiguousarray(x, dtype=np.float32)).cuda().to(dtype)
+
+
+def records():
+    """A tilted rig's map records as writable bytes and their G as [N][D][3][3]."""
+    rg = rig(3, N, D, W, H, 0.8 * W, 0.05, general=True)
+    raw = hsgd.hsgd_build_warps(rg["K_ref"], rg["K"], rg["R"], rg["t"], rg["depths"])
+    assert not any(r.is_shift for r in hsgd.warp_records(raw))
+    return raw, raw.view(np.float64)[:, :, :9].reshape(N, D, 3, 3)
+
+
+INF, NAN = np.inf, np.nan
+# entries of one plane's map: a position that is no number lies outside the plane, one at a
+# finite point over an infinite depth at the corner
+MAPS = {
+    "nan_scale": {(0, 0): NAN}, "nan_offset": {(1, 2): NAN}, "nan_depth": {(2, 2): NAN},
+    "inf_scale": {(0, 0): INF}, "minus_inf_offset": {(1, 2): -INF}, "inf_skew": {(0, 1): -INF},
+    "inf_depth": {(2, 2): INF}, "inf_over_inf": {(0, 2): INF, (2, 2): INF}, "nan_row": {(0, 0): NAN, (1, 1): NAN},
+    "tiny_depth": {(0, 2): 1.0, (1, 2): 1.0, (2, 0): 0.0, (2, 1): 0.0, (2, 2): 1e-310},
+}
+
+
+def broken(name):
+    raw, G = records()
+    for view, plane in ((0, 1), (1, 2)):
+        for (r, c), v in MAPS[name].items():
+            raw[view, plane, (3 * r + c) * 8:(3 * r + c + 1) * 8] = np.frombuffer(np.float64(v).tobytes(), np.uint8)
+    return hsgd.WarpTable(raw), raw.view(np.float64)[:, :, :9].reshape(N, D, 3, 3)
+
+
+@pytest.mark.parametrize("name", MAPS)
+def test_render_and_gradient_under_maps_that_are_no_numbers(name):
+    table, G = broken(name)
+    assert not table.shift_only
+    rng = np.random.default_rng(5)
+    M, I = f32(rng.uniform(0.05, 0.95, size=(D, H, W, 4))), f32(rng.uniform(size=(N, H, W, 3)))
+    with np.errstate(all="ignore"):
+        image = O.render(M, G)
+        want_loss, ref = O.loss_and_grad(M, G, I)
+    out, loss = hsgd.hsgd_render(dev(M), table, N, images=dev(I), want_loss=True)
+    assert np.abs(out.cpu().numpy() - image).max() <= 10 * (D + 2) * EPS
+    assert abs(loss.item() - want_loss) <= 1e-5 * want_loss
+    mask = hsgd.hsgd_select_active(dev(M), 2, with_ids=False)
+    for m, k, r in ((None, None, ref), (mask, 2, np.where(mask_bits(mask.cpu().numpy(), D)[..., None], ref, 0.0))):
+        g, loss = hsgd.hsgd_grad_step(dev(M), table, N, images=dev(I), mask=m, kcap=k, want_grad=True, want_loss=True)
+        assert abs(loss.item() - want_loss) <= 1e-5 * want_loss
+        assert np.abs(g.cpu().numpy() - r).max() <= (40 * (D + 2) + 8) * EPS * np.abs(r).max()
+
+
+@pytest.mark.parametrize("name", MAPS)
+def test_plane_sweep_under_maps_that_are_no_numbers(name):
+    table, G = broken(name)
+    I = f32(np.random.default_rng(6).uniform(size=(N, H, W, 3)))
+    with np.errstate(all="ignore"):
+        want = np.stack([np.stack([O.sample_bilinear(I[i], G[i, z]) for z in range(D)]) for i in range(N)])
+    got, = hsgd.hsgd_plane_sweep(dev(I), table, D, 1)
+    assert np.abs(got.cpu().numpy() - want).max() <= 10 * EPS
