@@ -655,7 +655,7 @@ __global__ __launch_bounds__(kGenThreads) __attribute__((amdgpu_waves_per_eu(4))
         for (int i = 0; i < 9; ++i) s_map[z][i] = m.g[i];
     }
     __syncthreads();
-    // rays that contribute; the other lanes sample like the rest and carry a zero residual
+    // rays that contribute; the other lanes sample like the rest and add zeros
     const bool own = lane < kGenOX && x < W && y < H;
     const double xd = (double)x, yd = (double)y;
     const size_t plane_bytes = (size_t)HW * S;
@@ -768,12 +768,13 @@ __global__ __launch_bounds__(kGenThreads) __attribute__((amdgpu_waves_per_eu(4))
             // a wave none of whose cells is selected has nothing to add, nor to pass on
             const bool some = __builtin_amdgcn_ballot_w64(s00[j] | s10[j] | s01[j] | s11[j]) != 0;
             if (some) {
-                const float ca = s.w * Tz[j];
+                // (without a ray the residual is zero, but zero times an infinite sample is not)
+                const float ca = own ? s.w * Tz[j] : 0.0f;
                 float4 gs;
                 gs.x = g0 * ca;
                 gs.y = g1 * ca;
                 gs.z = g2 * ca;
-                gs.w = Tz[j] * (g0 * (s.x - b0) + g1 * (s.y - b1) + g2 * (s.z - b2));
+                gs.w = own ? Tz[j] * (g0 * (s.x - b0) + g1 * (s.y - b1) + g2 * (s.z - b2)) : 0.0f;
                 const TapW w = tap_weights(fx[j], fy[j]);
                 const unsigned in = cell[j].in;
                 key = (in & 1u) ? cell[j].cell : kNone;

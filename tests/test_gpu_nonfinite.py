@@ -77,3 +77,35 @@ def test_plane_sweep_under_maps_that_are_no_numbers(name):
         want = np.stack([np.stack([O.sample_bilinear(I[i], G[i, z]) for z in range(D)]) for i in range(N)])
     got, = hsgd.hsgd_plane_sweep(dev(I), table, D, 1)
     assert np.abs(got.cpu().numpy() - want).max() <= 10 * EPS
+
+
+@pytest.mark.parametrize("bad", [INF, -INF, NAN])
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16], ids=["fp32", "bf16"])
+@pytest.mark.parametrize("k", [None, 2])
+def test_voxels_that_no_ray_of_the_frame_reads(k, dtype, bad):
+    """A shift by (-3.3, -2.4) under the general kernels: only rays past the frame's right and
+    lower edge would read the last columns and rows. They have no image, so whatever is stored
+    there, the gradient is what it is with ordinary numbers there, and zero in those cells."""
+    raw, _ = records()
+    G = np.tile(np.eye(3), (N, D, 1, 1))
+    G[..., 0, 2], G[..., 1, 2] = -3.3, -2.4
+    raw.view(np.float64)[:, :, :9] = G.reshape(N, D, 9)
+    table = hsgd.WarpTable(raw)
+    assert not table.shift_only
+    rng = np.random.default_rng(7)
+    M, I = f32(rng.uniform(0.05, 0.95, size=(D, H, W, 4))), f32(rng.uniform(size=(N, H, W, 3)))
+    if dtype == torch.bfloat16:
+        M = O.bf16_round(M)
+    want_loss, ref = O.loss_and_grad(M, G, I)
+    mask = hsgd.hsgd_select_active(dev(M, dtype), k, with_ids=False) if k else None
+    if k:
+        ref = np.where(mask_bits(mask.cpu().numpy(), D)[..., None], ref, 0.0)
+    unread = np.zeros((D, H, W), bool)
+    unread[:, :, W - 3:] = unread[:, H - 2:] = True
+    assert not ref[unread].any()
+    Md = dev(np.where(unread[..., None], bad, M), dtype)
+    g, loss = hsgd.hsgd_grad_step(Md, table, N, images=dev(I), mask=mask, kcap=k, want_grad=True, want_loss=True)
+    g = g.cpu().numpy()
+    assert abs(loss.item() - want_loss) <= 1e-5 * want_loss
+    assert not g[unread].any()
+    assert np.abs(g - ref).max() <= (40 * (D + 2) + 8) * EPS * np.abs(ref).max()
