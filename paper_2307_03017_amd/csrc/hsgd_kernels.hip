@@ -783,9 +783,15 @@ __global__ __launch_bounds__(kGenThreads) __attribute__((amdgpu_waves_per_eu(4))
                 v01 = scale4(w.w01, gs);
                 v10 = scale4(w.w10, gs);
                 v11 = scale4(w.w11, gs);
-                if (__builtin_amdgcn_ballot_w64(fy[j] == 0.0f)) {   // no weight below: nothing, whatever the adjoint
+                // a tap of no weight takes nothing, whatever the adjoint
+                if (__builtin_amdgcn_ballot_w64(fy[j] == 0.0f)) {
                     v01 = only_if(fy[j] != 0.0f, v01);
                     v11 = only_if(fy[j] != 0.0f, v11);
+                }
+                if (__builtin_amdgcn_ballot_w64(w.w00 == 0.0f)) {   // a fraction that rounded to 1
+                    v00 = only_if(w.w00 != 0.0f, v00);
+                    v10 = only_if(w.w10 != 0.0f, v10);
+                    v01 = only_if(w.w01 != 0.0f, v01);
                 }
                 // lane i takes lane i-1's right column where it is its own left column; where it
                 // is not, lane i-1 adds it to the cells by itself and sends zeros

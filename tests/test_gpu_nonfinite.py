@@ -109,3 +109,28 @@ def test_voxels_that_no_ray_of_the_frame_reads(k, dtype, bad):
     assert abs(loss.item() - want_loss) <= 1e-5 * want_loss
     assert not g[unread].any()
     assert np.abs(g - ref).max() <= (40 * (D + 2) + 8) * EPS * np.abs(ref).max()
+
+
+def test_taps_of_no_weight_take_nothing():
+    """A position a billionth left of and above a pixel: its fractions round to 1, so the pixel
+    itself has all the weight and the three cells beside it none. An infinite upstream value of
+    one ray reaches its own cell alone."""
+    raw, _ = records()
+    G = np.tile(np.eye(3), (N, D, 1, 1))
+    G[..., 0, 2] = G[..., 1, 2] = -1e-9
+    raw.view(np.float64)[:, :, :9] = G.reshape(N, D, 9)
+    table = hsgd.WarpTable(raw)
+    rng = np.random.default_rng(8)
+    M, up = dev(f32(rng.uniform(0.05, 0.95, size=(D, H, W, 4)))), dev(f32(rng.normal(size=(N, H, W, 3))))
+    cells = [(9, 11), (8, 62), (15, 40), (16, 63)]         # inside a tile and at its seams
+    for y, x in cells:
+        up[0, y, x] = 0.0
+    want, _ = hsgd.hsgd_grad_step(M, table, N, dimg=up, want_grad=True)
+    for y, x in cells:
+        up[0, y, x] = INF
+    got, _ = hsgd.hsgd_grad_step(M, table, N, dimg=up, want_grad=True)
+    rest = torch.ones((H, W), dtype=torch.bool, device="cuda")
+    for y, x in cells:
+        rest[y, x] = False
+        assert not torch.isfinite(got[:, y, x]).any()
+    assert torch.equal(got[:, rest], want[:, rest])
