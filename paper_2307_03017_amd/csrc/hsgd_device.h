@@ -181,6 +181,10 @@ __device__ __forceinline__ TapOffs tap_offsets(MapPos& p, int W, int H) {
     return tap_offsets<S>(p, W, H, c);
 }
 
+// Index of a workgroup in a grid that may continue in y (split_grid), and their number.
+__device__ __forceinline__ int flat_block() { return (int)(blockIdx.y * gridDim.x + blockIdx.x); }
+__device__ __forceinline__ int flat_blocks() { return (int)(gridDim.x * gridDim.y); }
+
 // Block index -> tile index so that each XCD (workgroups are dealt round-robin to the 8
 // XCDs) works on a contiguous run of tiles: the views of one tile and neighbouring tiles
 // share MPI lines in that XCD's L2.

@@ -416,7 +416,7 @@ __global__ __launch_bounds__(kBlock) void k_render(const void* __restrict__ mpi,
     constexpr int S = Vox<DT>::kBytes;
     __shared__ RowMap s_map[kTileH][kMaxD];
     __shared__ float sred[kBlock / 64];
-    const int tile = xcd_tile(blockIdx.x, gridDim.x);
+    const int tile = xcd_tile(flat_block(), flat_blocks());
     const int view = tile % N, t2 = tile / N;
     const int x0 = (t2 % ntx) * kTileW, y0 = (t2 / ntx) * kTileH;
     for (int i = threadIdx.x; i < kTileH * D; i += kBlock) {
@@ -643,7 +643,7 @@ __global__ __launch_bounds__(kGenThreads) __attribute__((amdgpu_waves_per_eu(4))
     __shared__ float4 s_low[2][kGenThreads];
     __shared__ GradStage s_stage[kGenY];
     __shared__ float sred[kGenY];
-    const int tile = xcd_tile(blockIdx.x, gridDim.x);
+    const int tile = xcd_tile(flat_block(), flat_blocks());
     const int view = tile % N, t2 = tile / N;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -2071,6 +2071,15 @@ int maxd_class(int D) {
     return kClasses[batch_class(D)];
 }
 
+// A grid dimension holds fewer than 2^32 threads (of a longer one the low 32 bits are launched,
+// without an error): the grid of `each` workgroups for every one of N views, the views split
+// evenly over y where they do not fit x (`each` alone always does).
+dim3 split_grid(int64_t each, int N, int threads) {
+    int rows = 1;
+    while (rows < N && (N % rows || each * (N / rows) * threads > (int64_t)UINT32_MAX)) ++rows;
+    return dim3((unsigned)(each * (N / rows)), (unsigned)rows);
+}
+
 #define HSGD_DISPATCH_D(D, BODY)                         \
     switch (maxd_class(D)) {                             \
         case 8: { constexpr int MD = 8; BODY; } break;   \
@@ -2149,12 +2158,13 @@ int launch_render(const hsgd_mpi& m, const hsgd_views& v, float* out_rgb, float*
                                                                             ntx)));
         }
     } else {
-        const dim3 grid((unsigned)ceil_div(m.W, kTileW), (unsigned)ceil_div(m.H, kTileH), (unsigned)v.N);
-        nparts = (int64_t)grid.x * grid.y * grid.z;
+        const int ntx = (int)ceil_div(m.W, kTileW);
+        const int64_t each = ntx * ceil_div(m.H, kTileH);
+        nparts = each * v.N;
         ProfScope ps(HSGD_K_RENDER, s);
-        HSGD_DISPATCH_T(m.dtype, hipLaunchKernelGGL((k_render<DT>), dim3((unsigned)nparts), dim3(kBlock), 0, s, m.rgba,
-                                                    m.D, m.H, m.W, v.N, v.warps, v.images, out_rgb, partials,
-                                                    (int)grid.x));
+        HSGD_DISPATCH_T(m.dtype, hipLaunchKernelGGL((k_render<DT>), split_grid(each, v.N, kBlock), dim3(kBlock), 0, s,
+                                                    m.rgba, m.D, m.H, m.W, v.N, v.warps, v.images, out_rgb, partials,
+                                                    ntx));
     }
     if (out_loss) {
         ProfScope ps(HSGD_K_REDUCE, s);
@@ -2208,8 +2218,9 @@ int launch_grad_step(const hsgd_mpi& m, const hsgd_views& v, const uint64_t* mas
                                slots, n);
         }
         const int ntx = (int)ceil_div(m.W, kGenOX);
-        nparts = ceil_div(m.H, kGenY) * ntx * v.N;
-        const dim3 grid((unsigned)nparts);
+        const int64_t each = ceil_div(m.H, kGenY) * ntx;
+        nparts = each * v.N;
+        const dim3 grid = split_grid(each, v.N, kGenThreads);
         ProfScope ps(HSGD_K_GRAD, s);
         const float* im = v.images;
         float* parts = out_loss ? partials : nullptr;

@@ -1,0 +1,53 @@
+"""Calls whose workgroups are 2^32 threads or more in all, which is more than one grid dimension
+holds (the runtime launches the low 32 bits of the product): long, narrow
+frames (2 columns in tiles of 63 or 64) of two views. Identity maps and one plane, so that a
+pixel's colour and gradient are its own voxel's: with weight 1 on one tap and 0 on the others
+a sample is the voxel exactly, a colour one product; a gradient entry is at most three products
+of numbers up to 1 and their sums over two views (8 roundings of values up to 6).
+"""
+
+import numpy as np
+import pytest
+import torch
+
+from paper_2307_03017_amd import hsgd
+
+pytestmark = pytest.mark.gpu
+
+W, H, N = 2, 1 << 25, 2
+BOUND = 8 * 6 * 2.0 ** -24
+
+
+def problem():
+    eye = np.eye(3)                           # the reference's own camera, N times
+    cameras = eye, np.stack([eye] * N), np.stack([eye] * N), np.zeros((N, 3)), np.ones(1)
+    table = hsgd.level_warps(*cameras, W, H, W, H)
+    gen = torch.Generator(device="cuda").manual_seed(1)
+    m = torch.rand((1, H, W, 4), generator=gen, device="cuda") * 0.5 + 0.25
+    images = torch.rand((N, H, W, 3), generator=gen, device="cuda")
+    return cameras, table, m, images
+
+
+def gradient(m, images):
+    c, a = m[0, ..., :3], m[0, ..., 3:]
+    r = sum(a * c - i for i in images) / N
+    return torch.cat([r * a, (r * c).sum(-1, keepdim=True)], dim=-1)[None]
+
+
+def squares(m, images):
+    colour = m[0, ..., 3:] * m[0, ..., :3]
+    return sum(((colour - i).double() ** 2).sum().item() for i in images) / (2 * N)
+
+
+def test_general_render_and_gradient():
+    _, table, m, images = problem()
+    maps = table.tensor                       # bare records: the general kernels
+    out, loss = hsgd.hsgd_render(m, maps, N, images=images, want_loss=True)
+    want = m[0, ..., 3:] * m[0, ..., :3]
+    assert all(torch.equal(o, want) for o in out)
+    total = squares(m, images)
+    assert abs(loss.item() - total) <= 1e-5 * total
+    del out, want
+    g, loss = hsgd.hsgd_grad_step(m, maps, N, images=images, want_grad=True, want_loss=True)
+    assert abs(loss.item() - total) <= 1e-5 * total
+    assert (g - gradient(m, images)).abs().max().item() <= BOUND
