@@ -1984,7 +1984,8 @@ __global__ __launch_bounds__(256) void k_convert(const void* __restrict__ src, v
 // batched serving step: kernels over the work items of every in-flight request
 // ------------------------------------------------------------------------------------
 // Each kernel is launched over exactly its items of the step: workgroup g takes item g of
-// the list concatenated over the requests.
+// the list concatenated over the requests (a list of 2^32 threads or more in rows over y, the
+// last of which may end past it).
 // Slot of flat work item g of kernel kk (prefix counts are non-decreasing; uniform result).
 __device__ __forceinline__ int batch_slot_of(const BatchTable* __restrict__ t, int kk, int g) {
     int s = 0;
@@ -2013,7 +2014,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(DT == HSGD_
     const BatchTable* __restrict__ t) {
     static_assert(64 * kUpWaves == 256, "one workgroup size");
     __shared__ typename UpAlpha<DT>::T s_a[MAXD][kUpPix];
-    const int g = blockIdx.x;
+    const int g = flat_block();
+    if (g >= t->total[BK_FRONT]) return;
     const int sl = batch_slot_of(t, BK_FRONT, g);
     const BatchSlot& b = t->slot[sl];
     const int j = g - t->pre[BK_FRONT][sl];
@@ -2044,7 +2046,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(DT == HSGD_
 template <int DT, int MAXD>
 __global__ __launch_bounds__(kSX * kSY) __attribute__((amdgpu_waves_per_eu(grad_shift_waves<DT, MAXD>()))) void k_batch_grad(
     const BatchTable* __restrict__ t, int kk) {
-    const int g = xcd_tile(blockIdx.x, gridDim.x);
+    const int total = t->total[kk];
+    if (flat_block() >= total) return;
+    const int g = xcd_tile(flat_block(), total);
     const int sl = batch_slot_of(t, kk, g);
     const BatchSlot& b = t->slot[sl];
     grad_shift_tile<DT, MAXD, true>(b.mpi, b.D, b.H, b.W, b.N, b.warps, b.images, nullptr, b.mask, b.kcap,
@@ -2078,6 +2082,12 @@ dim3 split_grid(int64_t each, int N, int threads) {
     int rows = 1;
     while (rows < N && (N % rows || each * (N / rows) * threads > (int64_t)UINT32_MAX)) ++rows;
     return dim3((unsigned)(each * (N / rows)), (unsigned)rows);
+}
+
+// The same for a list of n work items of a workgroup each: up to rows - 1 workgroups too many.
+dim3 items_grid(int64_t n, int threads) {
+    const int64_t rows = ceil_div(n * threads, (int64_t)UINT32_MAX - threads);
+    return dim3((unsigned)ceil_div(n, rows), (unsigned)rows);
 }
 
 #define HSGD_DISPATCH_D(D, BODY)                         \
@@ -2347,12 +2357,12 @@ int launch_batch_step(const BatchTable* staged, BatchTable* t, int dtype, hipStr
         shifts = std::max(shifts, (size_t)staged->slot[i].N * staged->slot[i].D);
     }
     HSGD_DISPATCH_T(dtype, HSGD_DISPATCH_D(max_d, hipLaunchKernelGGL((k_batch_front<DT, MD>),
-                                                                     dim3((unsigned)staged->total[BK_FRONT]), dim3(256), 0,
+                                                                     items_grid(staged->total[BK_FRONT], 256), dim3(256), 0,
                                                                      s, t)));
     for (int c = 0; c < kNumClasses; ++c)
         if (staged->total[BK_GRAD + c])
             HSGD_DISPATCH_T(dtype, HSGD_DISPATCH_D(kClasses[c], hipLaunchKernelGGL((k_batch_grad<DT, MD>),
-                                                                                   dim3((unsigned)staged->total[BK_GRAD + c]),
+                                                                                   items_grid(staged->total[BK_GRAD + c], kSX * kSY),
                                                                                    dim3(kSX * kSY), 0, s, t, BK_GRAD + c)));
     HSGD_DISPATCH_T(dtype, hipLaunchKernelGGL((k_batch_update<DT>), dim3((unsigned)staged->total[BK_UPDATE]), dim3(256),
                                               sizeof(int2) * shifts, s, t));

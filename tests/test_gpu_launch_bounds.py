@@ -51,3 +51,18 @@ def test_general_render_and_gradient():
     g, loss = hsgd.hsgd_grad_step(m, maps, N, images=images, want_grad=True, want_loss=True)
     assert abs(loss.item() - total) <= 1e-5 * total
     assert (g - gradient(m, images)).abs().max().item() <= BOUND
+
+
+def test_batched_step():
+    cameras, _, m, images = problem()
+    batch = hsgd.Batch(1, 1, N, H, W, 1, dtype=torch.float32)
+    st = hsgd.ServingStream(0, *cameras, W, H, (1,), 1, dtype=torch.float32,
+                            lr_rgb=0.25, lr_alpha=0.25)
+    st.levels[0].copy_(m)
+    st.images[0].copy_(images)
+    assert batch.admit(st) is not None
+    assert batch.step()[0] == 1
+    want = (m - 0.25 * gradient(m, images)).clamp_(0.0, 1.0)
+    assert (st.result - want).abs().max().item() <= BOUND
+    total = squares(m, images)
+    assert abs(st.loss_log[0].item() - total) <= 1e-5 * total
