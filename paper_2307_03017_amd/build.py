@@ -9,8 +9,10 @@ Objects go to _build/ at the repository root; the shared library lands next to t
 from __future__ import annotations
 
 import os
+import re
 import subprocess
 import sys
+import tempfile
 from concurrent.futures import ThreadPoolExecutor
 
 PKG = os.path.dirname(os.path.abspath(__file__))
@@ -53,6 +55,27 @@ def _run(cmd):
     return r.stdout
 
 
+def register_shifts(obj: str) -> list:
+    """Vector 64-bit shifts by a register in a built object's device code, as "kernel: shift"
+    (csrc/hsgd_device.h, lane_bit, says why there must be none)."""
+    objdump = os.path.join(os.path.dirname(os.path.dirname(HIPCC)), "llvm", "bin", "llvm-objdump")
+    found, kernel = [], ""
+    with tempfile.TemporaryDirectory() as d:
+        os.symlink(os.path.abspath(obj), os.path.join(d, "o"))     # (it extracts beside its input)
+        subprocess.run([objdump, "--offloading", "o"], cwd=d, check=True, stdout=subprocess.DEVNULL)
+        for code in sorted(f for f in os.listdir(d) if f.endswith(ARCH)):
+            text = subprocess.run([objdump, "-d", "--no-show-raw-insn", code], cwd=d, check=True, text=True,
+                                  stdout=subprocess.PIPE).stdout
+            for line in text.splitlines():
+                head = re.match(r"[0-9a-f]+ <(\S+)>:", line)
+                if head:
+                    kernel = head[1]
+                shift = re.match(r"\s+(v_(?:lshl|lshr|ashr)rev_[bi]64\S*\s+\S+ [va]\d+,.*?)\s*//", line)
+                if shift:
+                    found.append(f"{kernel}: {shift[1]}")
+    return found
+
+
 def build(verbose: bool = False) -> str:
     """Compile every source and link libhsgd.so; returns its path."""
     os.makedirs(BUILD, exist_ok=True)
@@ -72,6 +95,9 @@ def build(verbose: bool = False) -> str:
         for o in outs:
             if o.strip():
                 print(o)
+    shifts = [s for (src, kind), (_, obj) in zip(SOURCES, jobs) if kind == "device" for s in register_shifts(obj)]
+    if shifts:
+        raise RuntimeError("64-bit vector shifts by a register, which can give wrong bits:\n" + "\n".join(shifts))
     tmp = LIB + ".tmp"
     _run([HIPCC, f"--offload-arch={ARCH}", "-shared", "-fPIC", "-o", tmp,
           *[o for _, o in jobs], "-L/opt/rocm/lib", "-lamdhip64"])

@@ -200,7 +200,7 @@ __device__ __forceinline__ uint64_t topk_bits(const float (&A)[MAXD], int D, int
             bestA = b ? A[z] : bestA;
         }
         const int lo = min(max(best - (kk - 1) / 2, 0), D - kk);
-        sel = (kk == 64 ? ~0ull : ((1ull << kk) - 1)) << lo;
+        sel = lane_bits_below(lo + kk) & ~lane_bits_below(lo);
     } else if (2 * kk <= D) {
         // kk passes: the best remaining score, the nearer plane on equal scores
         for (int j = 0; j < kk; ++j) {
@@ -212,7 +212,7 @@ __device__ __forceinline__ uint64_t topk_bits(const float (&A)[MAXD], int D, int
                 best = b ? z : best;
                 bestA = b ? A[z] : bestA;
             }
-            sel |= 1ull << best;
+            sel |= lane_bit(best);
         }
     } else {
         // D - kk passes removing the worst: the lowest score, the farther plane on ties
@@ -226,7 +226,7 @@ __device__ __forceinline__ uint64_t topk_bits(const float (&A)[MAXD], int D, int
                 worst = b ? z : worst;
                 worstA = b ? A[z] : worstA;
             }
-            out |= 1ull << worst;
+            out |= lane_bit(worst);
         }
         sel = full & ~out;
     }
@@ -384,13 +384,13 @@ __global__ __launch_bounds__(256) void k_compact(const uint64_t* __restrict__ ba
     const int64_t wblk = (int64_t)p >> 6;
     if (wblk >= nblk) return;   // whole waves only
     const int lane = threadIdx.x & 63;
-    const uint64_t lt = (1ull << lane) - 1;
     for (int z = 0; z < D; ++z) {
         const int64_t e = (int64_t)z * nblk + wblk;
         const uint64_t b = bal[e];
         const int base = off[e] + seg[e / kSeg];
-        if ((b >> lane) & 1) {
-            const int64_t pos = (int64_t)base + __popcll(b & lt);
+        if (has_lane_bit(b, lane)) {
+            const int64_t pos = (int64_t)base + __builtin_amdgcn_mbcnt_hi((unsigned)(b >> 32),
+                                                                          __builtin_amdgcn_mbcnt_lo((unsigned)b, 0u));
             if (pos < cap) ids[pos] = z * HW + p;
         }
         if (lane == 0) off[e] = base;
@@ -504,13 +504,6 @@ __global__ __launch_bounds__(256) void k_reduce(const float* __restrict__ partia
 // ------------------------------------------------------------------------------------
 __device__ __forceinline__ uint64_t plane_bits(int D) { return D == 64 ? ~0ull : ((1ull << D) - 1); }
 
-// rank of plane z in mask word m, or -1 when (z, p) is not selected or beyond kcap
-__device__ __forceinline__ int slot_rank(uint64_t m, int z, int kcap) {
-    if (!((m >> z) & 1)) return -1;
-    const int r = __popcll(m & ((1ull << z) - 1));
-    return r < kcap ? r : -1;
-}
-
 // ------------------------------------------------------------------------------------
 // gradient, general warps: per-ray scans, transposed-bilinear scatter with atomics
 //
@@ -557,15 +550,11 @@ __device__ __forceinline__ float4 scale4(float w, const float4& g) {
     return make_float4(w * g.x, w * g.y, w * g.z, w * g.w);
 }
 
-// slot_rank for a plane that differs by lane, in 32-bit steps. (A 64-bit shift by a VGPR that
-// is the last of the kernel's allocation gave wrong bits now and then: with 128 registers and
-// the amount in v127, entries of the ring below were dropped.)
+// Slot rank of plane z (it differs by lane) among the pixel's selected planes, or -1 (not
+// selected, or ranked kcap and beyond).
 __device__ __forceinline__ int slot_rank_lane(uint64_t m, unsigned z, int kcap) {
-    const unsigned lo = (unsigned)m, hi = (unsigned)(m >> 32);
-    const bool far = z >= 32u;
-    const unsigned w = far ? hi : lo, b = 1u << (z & 31u);
-    const int r = __popc(w & (b - 1u)) + (far ? __popc(lo) : 0);
-    return (w & b) != 0u && r < kcap ? r : -1;
+    const int r = __popcll(m & lane_bits_below(z));
+    return has_lane_bit(m, z) && r < kcap ? r : -1;
 }
 
 // What one lane wrote to LDS before this another lane of the wave reads after it (the LDS

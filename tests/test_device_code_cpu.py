@@ -1,0 +1,26 @@
+"""What the built device code must not contain, and that the build sees it. (A vector 64-bit shift
+whose amount is the last register of a wave's allocation gives wrong bits, so no kernel shifts 64
+bits by a register.)
+"""
+
+import subprocess
+
+from paper_2307_03017_amd import build, hsgd
+
+
+def test_no_kernel_shifts_64_bits_by_a_register():
+    hsgd.lib()                                 # says so if the library has not been built
+    assert build.register_shifts(build.LIB) == []
+
+
+def test_such_a_shift_is_seen(tmp_path):
+    """One kernel with a lane's bit of a mask as the compiler makes it, one with a wave's."""
+    src, obj = tmp_path / "shift.hip", tmp_path / "shift.o"
+    src.write_text("""#include <hip/hip_runtime.h>
+__global__ void by_lane(unsigned long long* p) { p[threadIdx.x] = 1ull << (p[threadIdx.x] & 63); }
+__global__ void by_wave(unsigned long long* p, int n) { p[threadIdx.x] <<= n & 63; }
+""")
+    subprocess.run([build.HIPCC, *build.DEVICE_FLAGS, "-c", str(src), "-o", str(obj)], check=True,
+                   stderr=subprocess.DEVNULL)
+    found = build.register_shifts(str(obj))
+    assert len(found) == 1 and "by_lane" in found[0] and "v_lshlrev_b64" in found[0]
