@@ -44,6 +44,14 @@ __device__ __forceinline__ bool has_lane_bit(uint64_t m, unsigned z) {
     return (((z < 32u ? (uint32_t)m : hi) >> (z & 31u)) & 1u) != 0u;
 }
 
+// What one lane wrote to LDS before this another lane of the wave reads after it (the LDS
+// operations of a wave execute in order; this keeps the compiler from moving them).
+__device__ __forceinline__ void wave_lds_fence() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    asm volatile("" ::: "memory");
+}
+
 // Raw (untyped, stride 0) buffer resource over one MPI row of n_bytes bytes: loads at
 // offsets outside [0, n_bytes) return 0, which is the zero padding of a plane outside the
 // image; n_bytes = 0 makes a whole row read as padding. Word 3 selects the 32-bit data

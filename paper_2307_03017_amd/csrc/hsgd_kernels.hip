@@ -557,14 +557,6 @@ __device__ __forceinline__ int slot_rank_lane(uint64_t m, unsigned z, int kcap) 
     return has_lane_bit(m, z) && r < kcap ? r : -1;
 }
 
-// What one lane wrote to LDS before this another lane of the wave reads after it (the LDS
-// operations of a wave execute in order; this keeps the compiler from moving them).
-__device__ __forceinline__ void wave_lds_fence() {
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    asm volatile("" ::: "memory");
-}
-
 // One wave's cells on their way to the slots: a ring of values and the cells they go to
 // (cell | plane << 26: H W <= 2^26 and z < 64), emptied 64 at a time. Emptying reads a mask
 // word per lane to find each cell's slot, so that a stray cell, whose word nobody loaded

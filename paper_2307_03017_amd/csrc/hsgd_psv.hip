@@ -163,7 +163,7 @@ __device__ __forceinline__ void psv_sample_general(const float* __restrict__ im,
         s_row[wv][lane][1] = m.b1;
         s_row[wv][lane][2] = m.b2;
     }
-    __builtin_amdgcn_wave_barrier();
+    wave_lds_fence();
     RowMap m = psv_row(wp, 0);                              // its a0, a1, a2
     MapPos p[4];
     float3 a[4], b[4], c[4], d[4];

@@ -3,6 +3,8 @@ whose amount is the last register of a wave's allocation gives wrong bits, so no
 bits by a register.)
 """
 
+import glob
+import os
 import subprocess
 
 from paper_2307_03017_amd import build, hsgd
@@ -24,3 +26,15 @@ __global__ void by_wave(unsigned long long* p, int n) { p[threadIdx.x] <<= n & 6
                    stderr=subprocess.DEVNULL)
     found = build.register_shifts(str(obj))
     assert len(found) == 1 and "by_lane" in found[0] and "v_lshlrev_b64" in found[0]
+
+
+def test_a_wave_hands_over_lds_by_the_fence():
+    """The builtin barrier of a wave orders no memory: the compiler may move another lane's loads
+    before it. It stands in wave_lds_fence alone, between the fence and the clobber that do."""
+    uses = []
+    for path in sorted(glob.glob(os.path.join(build.CSRC, "*"))):
+        lines = open(path).read().splitlines()
+        uses += [(os.path.basename(path), lines[i - 1].strip(), lines[i + 1].strip())
+                 for i, line in enumerate(lines) if "__builtin_amdgcn_wave_barrier" in line]
+    assert uses == [("hsgd_device.h", '__builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");',
+                     'asm volatile("" ::: "memory");')]
