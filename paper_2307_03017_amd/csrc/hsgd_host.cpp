@@ -112,6 +112,33 @@ RenderWs render_ws(int H, int W, int N) {
     return w;
 }
 
+// More rows per wave load each plane row fewer times and prepare addresses and weights less
+// often; but they leave fewer waves, each with more to do one after another, and rows past the
+// frame's last one are computed for nothing. In workgroups of single rows (8 waves of a row),
+// from calls of 200 sizes (40x10 to 1920x1080, 4 to 64 planes, 1 to 64 views) in both storages,
+// single rows against four, us (FP32 where nothing else is said):
+//  - many views: 16.2 and 18.7 at 624 workgroups (109x208x32, 12 views, BF16), 15.8 and 17.8 at
+//    576 (512x12x32, 32), 21.4 and 18.5 at 1075 (255x341x24, 5);
+//  - two to four views, whose plane rows are more often not yet in a cache: 12.8 and 13.9 at 477
+//    (129x418x32, 3), 42.1 and 33.5 at 700 (270x558x64, 2);
+//  - one view: 12.4 and 19.9 at 248 (86x985x48), 32.6 and 26.3 at 301 (406x344x64), 18.6 and 17.4
+//    at 432 (512x384x32); under 24 planes 10.7 and 11.2 at 456 (448x450x16);
+//  - under 16 planes a call is bound by its launch below some 1536: 13.1 and 14.0 at 1150
+//    (1425x195x8, 2), 51.2 and 35.6 at 10368;
+//  - padding: 21.0 and 25.3 at 864 (512x24x32, 32, BF16), where a quarter of four rows' work is
+//    past the frame.
+// Eight rows pay from 1536 of their workgroups on: 73 us against 67 by four at 384 (1008x756x32,
+// one view), 105 against 113 at 1944 (512x384x32, 18).
+int render_rows(int D, int H, int W, int N) {
+    const int64_t ntx = ceil_div(W, kShiftRX) * N;
+    const int64_t n1 = ntx * ceil_div(H, kShiftRY);
+    const int64_t n4 = ntx * ceil_div(H, 4 * kRenderWaves);
+    const int64_t n8 = ntx * ceil_div(H, 8 * kRenderWaves);
+    if (n8 >= 1536 && 10 * n4 >= 17 * n8) return 8;
+    const int64_t least = D < 16 ? 1536 : N > 4 ? 768 : N > 1 || D < 24 ? 640 : 300;
+    return n1 >= least && 10 * n1 >= 17 * n4 ? 4 : 1;
+}
+
 GradWs grad_ws(int D, int H, int W, int N, int kcap) {
     (void)D;
     GradWs w{};

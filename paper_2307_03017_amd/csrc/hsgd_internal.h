@@ -24,6 +24,8 @@ constexpr int kShiftOY = 7;
 // supplies the right-hand taps of lane 62).
 constexpr int kShiftRX = 63;
 constexpr int kShiftRY = 8;
+// Waves of a translation-render workgroup that takes several rows of rays per wave.
+constexpr int kRenderWaves = 4;
 // Source columns of one 2 x 2 upsampling workgroup (a wave less its two halo lanes).
 constexpr int kUpCols = 62;
 
@@ -69,6 +71,8 @@ struct RenderWs {
     int64_t nparts;
 };
 RenderWs render_ws(int H, int W, int N);
+// Rows of rays a wave of the translation render takes: 1, 4 or 8.
+int render_rows(int D, int H, int W, int N);
 
 // grad_step: FP32 gradient slots, one rank-major slice [kcap][H*W] of float4 per view,
 // and the loss partials.

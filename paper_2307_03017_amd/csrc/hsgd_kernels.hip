@@ -1330,12 +1330,6 @@ __global__ __launch_bounds__(kSX * kSY) void k_render_shift(const void* __restri
 // two rows of rays it lies between instead of twice, and the plane's addresses and weights are
 // prepared once for R rows. FP32, 512 x 384 x 32, 18 views: 175 us by single rows, 132 at R = 2,
 // 118 at 4, 114 at 8; BF16, 1440 x 1080 x 64, 5 views: 802, 679, 638, 570.
-constexpr int kRenderWaves = 4;
-// Fewer waves leave the chip idle: at 216 workgroups of R = 4 (512 x 384 x 32, one view) 17.2 us
-// against 18.5 by single rows, at 120 (256 x 192 x 48, two) 20.3 against 16.0; at 384 of R = 8
-// (1008 x 756 x 32, one) 74 us against 68 at R = 4, at 1944 (the 18 views) 114 against 118.
-constexpr int64_t kRender4Min = 192;
-constexpr int64_t kRender8Min = 1536;
 template <int DT, int R>
 __global__ __launch_bounds__(64 * kRenderWaves) void k_render_shift_rows(
     const void* __restrict__ mpi, int D, int H, int W, int N, const hsgd_warp* __restrict__ warps,
@@ -2129,19 +2123,20 @@ int launch_render(const hsgd_mpi& m, const hsgd_views& v, float* out_rgb, float*
     if (v.flags & HSGD_VIEWS_SHIFT_ONLY) {
         const int ntx = (int)ceil_div(m.W, kShiftRX), nty = (int)ceil_div(m.H, kShiftRY);
         nparts = (int64_t)ntx * nty * v.N;
-        const int64_t n4 = (int64_t)ntx * ceil_div(m.H, 4 * kRenderWaves) * v.N;
-        const int64_t n8 = (int64_t)ntx * ceil_div(m.H, 8 * kRenderWaves) * v.N;
+        const int rows = render_rows(m.D, m.H, m.W, v.N);
         ProfScope ps(HSGD_K_RENDER, s);
-        if (n8 >= kRender8Min) {
-            nparts = n8;
-            HSGD_DISPATCH_T(m.dtype, hipLaunchKernelGGL((k_render_shift_rows<DT, 8>), dim3((unsigned)n8),
-                                                        dim3(64 * kRenderWaves), 0, s, m.rgba, m.D, m.H, m.W, v.N,
-                                                        v.warps, v.images, out_rgb, partials, ntx));
-        } else if (n4 >= kRender4Min) {
-            nparts = n4;
-            HSGD_DISPATCH_T(m.dtype, hipLaunchKernelGGL((k_render_shift_rows<DT, 4>), dim3((unsigned)n4),
-                                                        dim3(64 * kRenderWaves), 0, s, m.rgba, m.D, m.H, m.W, v.N,
-                                                        v.warps, v.images, out_rgb, partials, ntx));
+        if (rows > 1) {
+            nparts = (int64_t)ntx * ceil_div(m.H, rows * kRenderWaves) * v.N;
+#define HSGD_RENDER_ROWS(R)                                                                                        \
+    HSGD_DISPATCH_T(m.dtype, hipLaunchKernelGGL((k_render_shift_rows<DT, R>), dim3((unsigned)nparts),                \
+                                                dim3(64 * kRenderWaves), 0, s, m.rgba, m.D, m.H, m.W, v.N, v.warps, \
+                                                v.images, out_rgb, partials, ntx))
+            if (rows == 8) {
+                HSGD_RENDER_ROWS(8);
+            } else {
+                HSGD_RENDER_ROWS(4);
+            }
+#undef HSGD_RENDER_ROWS
         } else {
             HSGD_DISPATCH_T(m.dtype, HSGD_DISPATCH_D(m.D, hipLaunchKernelGGL((k_render_shift<DT, MD>), dim3((unsigned)nparts),
                                                                             dim3(kSX * kSY), 0, s, m.rgba, m.D, m.H, m.W,
