@@ -3,7 +3,7 @@
 
 #include <hip/hip_runtime.h>
 
-#include "hsgd.h"
+#include "hsgd_internal.h"
 
 namespace hsgd {
 namespace {
@@ -212,7 +212,21 @@ __device__ __forceinline__ TapOffs tap_offsets(MapPos& p, int W, int H) {
     return tap_offsets<S>(p, W, H, c);
 }
 
-// Index of a workgroup in a grid that may continue in y (split_grid), and their number.
+// A grid dimension holds fewer than 2^32 threads; of a longer one the runtime launches the low
+// 32 bits, without an error. Longer grids therefore go on in y.
+// The grid of `each` workgroups for every one of N views, the views split evenly over y where
+// they do not fit x (`each` alone must).
+inline dim3 split_grid(int64_t each, int N, int threads) {
+    int rows = 1;
+    while (rows < N && (N % rows || each * (N / rows) * threads > (int64_t)UINT32_MAX)) ++rows;
+    return dim3((unsigned)(each * (N / rows)), (unsigned)rows);
+}
+// The grid of n workgroups, with up to rows - 1 too many, which return at once.
+inline dim3 items_grid(int64_t n, int threads) {
+    const int64_t rows = ceil_div(n * threads, (int64_t)UINT32_MAX - threads);
+    return dim3((unsigned)ceil_div(n, rows), (unsigned)rows);
+}
+// Index of a workgroup in either grid, and the first's number of workgroups.
 __device__ __forceinline__ int flat_block() { return (int)(blockIdx.y * gridDim.x + blockIdx.x); }
 __device__ __forceinline__ int flat_blocks() { return (int)(gridDim.x * gridDim.y); }
 

@@ -1216,7 +1216,7 @@ __global__ __launch_bounds__(kSX * kSY) __attribute__((amdgpu_waves_per_eu(grad_
     const float* __restrict__ images, const float* __restrict__ dimg, const uint64_t* __restrict__ mask,
     int kcap, float inv_n, float4* __restrict__ slots, float* __restrict__ partials, int ntx) {
     grad_shift_tile<DT, MAXD, MASKED>(mpi, D, H, W, N, warps, images, dimg, mask, kcap, inv_n, slots, partials,
-                                      ntx, xcd_tile(blockIdx.x, gridDim.x), threadIdx.x);
+                                      ntx, xcd_tile(flat_block(), flat_blocks()), threadIdx.x);
 }
 
 // ------------------------------------------------------------------------------------
@@ -1946,7 +1946,7 @@ __global__ __launch_bounds__(256) void k_downsample(const float* __restrict__ im
 template <int SDT, int DDT>
 __global__ __launch_bounds__(256) void k_convert(const void* __restrict__ src, void* __restrict__ dst,
                                                  int64_t n) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int64_t i = (int64_t)flat_block() * 256 + threadIdx.x;
     if (i >= n) return;
     float v;
     if (SDT == HSGD_FP32) v = reinterpret_cast<const float*>(src)[i];
@@ -2048,21 +2048,6 @@ __global__ __launch_bounds__(256) void k_batch_update(const BatchTable* __restri
 constexpr int kClasses[kNumClasses] = {8, 16, 24, 32, 40, 48, 64};
 int maxd_class(int D) {
     return kClasses[batch_class(D)];
-}
-
-// A grid dimension holds fewer than 2^32 threads (of a longer one the low 32 bits are launched,
-// without an error): the grid of `each` workgroups for every one of N views, the views split
-// evenly over y where they do not fit x (`each` alone always does).
-dim3 split_grid(int64_t each, int N, int threads) {
-    int rows = 1;
-    while (rows < N && (N % rows || each * (N / rows) * threads > (int64_t)UINT32_MAX)) ++rows;
-    return dim3((unsigned)(each * (N / rows)), (unsigned)rows);
-}
-
-// The same for a list of n work items of a workgroup each: up to rows - 1 workgroups too many.
-dim3 items_grid(int64_t n, int threads) {
-    const int64_t rows = ceil_div(n * threads, (int64_t)UINT32_MAX - threads);
-    return dim3((unsigned)ceil_div(n, rows), (unsigned)rows);
 }
 
 #define HSGD_DISPATCH_D(D, BODY)                         \
@@ -2180,8 +2165,9 @@ int launch_grad_step(const hsgd_mpi& m, const hsgd_views& v, const uint64_t* mas
         const int ntx = (int)ceil_div(m.W + 1, kOX), nty = (int)ceil_div(m.H + 1, kOY);
         cover_w = ntx * kOX;
         cover_h = nty * kOY;
-        nparts = (int64_t)ntx * nty * v.N;
-        const dim3 grid((unsigned)nparts);
+        const int64_t each = (int64_t)ntx * nty;
+        nparts = each * v.N;
+        const dim3 grid = split_grid(each, v.N, kSX * kSY);
         ProfScope ps(HSGD_K_GRAD, s);
         if (mask) {
             HSGD_DISPATCH_T(m.dtype, HSGD_DISPATCH_D(m.D, hipLaunchKernelGGL((k_grad_shift<DT, MD, true>), grid,
@@ -2305,7 +2291,7 @@ int launch_downsample(const float* img, int N, int H, int W, float* out, hipStre
 }
 
 int launch_convert(const void* src, int sdt, void* dst, int ddt, size_t n, hipStream_t s) {
-    const dim3 grid((unsigned)ceil_div((int64_t)n, 256));
+    const dim3 grid = items_grid(ceil_div((int64_t)n, 256), 256);
     ProfScope ps(HSGD_K_CONVERT, s);
     if (sdt == HSGD_FP32 && ddt == HSGD_FP32)
         hipLaunchKernelGGL((k_convert<HSGD_FP32, HSGD_FP32>), grid, dim3(256), 0, s, src, dst, (int64_t)n);

@@ -246,12 +246,13 @@ __device__ __forceinline__ void psv_tile_levels(const float3 (&v)[4], float* __r
 template <bool SHIFT, int L, int OT>
 __global__ __launch_bounds__(256) void k_plane_sweep(const float* __restrict__ img,
                                                      const hsgd_warp* __restrict__ warps, int D, int H, int W,
-                                                     PsvOut out, int ntx, int nty) {
+                                                     PsvOut out, int ntx, int nty, int nb) {
     // levels 0.. of the tile, packed one after another: 3 * (1024 + 256 + 64 + 16 + 4)
     // floats; before them, the source patch of a translation map (3315 floats)
     __shared__ __align__(16) float s_lv[3 * (1024 + 256 + 64 + 16 + 4)];
     static_assert(kPsvSrcN <= 3 * (1024 + 256 + 64 + 16 + 4), "source patch exceeds the LDS tile");
-    const int b = xcd_tile(blockIdx.x, gridDim.x);
+    if (flat_block() >= nb) return;
+    const int b = xcd_tile(flat_block(), nb);
     const int tx = b % ntx, r = b / ntx;
     const int z = r % D, r2 = r / D;
     const int ty = r2 % nty, i = r2 / nty;
@@ -286,11 +287,11 @@ int launch_plane_sweep(const hsgd_views& src, int D, int L, int out_dtype, void*
     const bool shift = (src.flags & HSGD_VIEWS_SHIFT_ONLY) != 0;
 #define HSGD_PSV_LAUNCH(SH, LV)                                                                               \
     if (out_dtype == HSGD_FP32)                                                                               \
-        hipLaunchKernelGGL((k_plane_sweep<SH, LV, HSGD_FP32>), dim3((unsigned)nb), dim3(256), 0, s, src.images, \
-                           src.warps, D, src.H, src.W, o, ntx, nty);                                          \
+        hipLaunchKernelGGL((k_plane_sweep<SH, LV, HSGD_FP32>), items_grid(nb, 256), dim3(256), 0, s, src.images, \
+                           src.warps, D, src.H, src.W, o, ntx, nty, (int)nb);                                          \
     else                                                                                                      \
-        hipLaunchKernelGGL((k_plane_sweep<SH, LV, HSGD_BF16>), dim3((unsigned)nb), dim3(256), 0, s, src.images, \
-                           src.warps, D, src.H, src.W, o, ntx, nty)
+        hipLaunchKernelGGL((k_plane_sweep<SH, LV, HSGD_BF16>), items_grid(nb, 256), dim3(256), 0, s, src.images, \
+                           src.warps, D, src.H, src.W, o, ntx, nty, (int)nb)
     switch (L * 2 + (shift ? 1 : 0)) {
         case 2: HSGD_PSV_LAUNCH(false, 1); break;
         case 3: HSGD_PSV_LAUNCH(true, 1); break;

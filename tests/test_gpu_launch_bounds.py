@@ -1,6 +1,6 @@
 """Calls whose workgroups are 2^32 threads or more in all, which is more than one grid dimension
-holds (the runtime launches the low 32 bits of the product): long, narrow
-frames (2 columns in tiles of 63 or 64) of two views. Identity maps and one plane, so that a
+holds (the runtime launches the low 32 bits of the product): long, narrow frames (2 columns in
+tiles of 62 to 64), and a conversion of as many values. Identity maps and one plane, so that a
 pixel's colour and gradient are its own voxel's: with weight 1 on one tap and 0 on the others
 a sample is the voxel exactly, a colour one product; a gradient entry is at most three products
 of numbers up to 1 and their sums over two views (8 roundings of values up to 6).
@@ -66,3 +66,28 @@ def test_batched_step():
     assert (st.result - want).abs().max().item() <= BOUND
     total = squares(m, images)
     assert abs(st.loss_log[0].item() - total) <= 1e-5 * total
+
+
+def test_translation_gradient():
+    _, table, m, images = problem()
+    assert table.shift_only
+    g, loss = hsgd.hsgd_grad_step(m, table, N, images=images, want_grad=True, want_loss=True)
+    total = squares(m, images)
+    assert abs(loss.item() - total) <= 1e-5 * total
+    assert (g - gradient(m, images)).abs().max().item() <= BOUND
+
+
+@pytest.mark.parametrize("general", [False, True], ids=["translation", "general"])
+def test_plane_sweep(general):
+    D, h = 64, 5 << 20
+    eye = np.eye(3)
+    table = hsgd.psv_warps(eye, eye[None], eye[None], np.zeros((1, 3)), np.linspace(1.0, 2.0, D))
+    images = torch.rand((1, h, W, 3), device="cuda")
+    out, = hsgd.hsgd_plane_sweep(images, table.tensor if general else table, D, dtype=torch.bfloat16)
+    want = images[0].to(torch.bfloat16)
+    assert all(torch.equal(plane, want) for plane in out[0])
+
+
+def test_conversion():
+    src = torch.rand((1 << 32) + 4097, device="cuda")
+    assert torch.equal(hsgd.hsgd_convert(src, torch.bfloat16), src.to(torch.bfloat16))
