@@ -4,6 +4,8 @@
 //                 downsampled level by level (Sec. 3.2, Hierarchical PSV Construction)
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+
 #include "hsgd_device.h"
 #include "hsgd_internal.h"
 
@@ -246,13 +248,12 @@ __device__ __forceinline__ void psv_tile_levels(const float3 (&v)[4], float* __r
 template <bool SHIFT, int L, int OT>
 __global__ __launch_bounds__(256) void k_plane_sweep(const float* __restrict__ img,
                                                      const hsgd_warp* __restrict__ warps, int D, int H, int W,
-                                                     PsvOut out, int ntx, int nty, int nb) {
+                                                     PsvOut out, int ntx, int nty) {
     // levels 0.. of the tile, packed one after another: 3 * (1024 + 256 + 64 + 16 + 4)
     // floats; before them, the source patch of a translation map (3315 floats)
     __shared__ __align__(16) float s_lv[3 * (1024 + 256 + 64 + 16 + 4)];
     static_assert(kPsvSrcN <= 3 * (1024 + 256 + 64 + 16 + 4), "source patch exceeds the LDS tile");
-    if (flat_block() >= nb) return;
-    const int b = xcd_tile(flat_block(), nb);
+    const int b = xcd_tile(blockIdx.x, gridDim.x);
     const int tx = b % ntx, r = b / ntx;
     const int z = r % D, r2 = r / D;
     const int ty = r2 % nty, i = r2 / nty;
@@ -278,20 +279,18 @@ __global__ __launch_bounds__(256) void k_plane_sweep(const float* __restrict__ i
 
 }  // namespace
 
-int launch_plane_sweep(const hsgd_views& src, int D, int L, int out_dtype, void* const* out, hipStream_t s) {
-    const int ntx = (int)ceil_div(src.W, kPsvTW), nty = (int)ceil_div(src.H, kPsvTH);
-    const int64_t nb = (int64_t)ntx * nty * src.N * D;
-    PsvOut o{};
-    for (int l = 0; l < L; ++l) o.p[l] = out[l];
-    ProfScope ps(HSGD_K_PSV, s);
-    const bool shift = (src.flags & HSGD_VIEWS_SHIFT_ONLY) != 0;
-#define HSGD_PSV_LAUNCH(SH, LV)                                                                               \
-    if (out_dtype == HSGD_FP32)                                                                               \
-        hipLaunchKernelGGL((k_plane_sweep<SH, LV, HSGD_FP32>), items_grid(nb, 256), dim3(256), 0, s, src.images, \
-                           src.warps, D, src.H, src.W, o, ntx, nty, (int)nb);                                          \
-    else                                                                                                      \
-        hipLaunchKernelGGL((k_plane_sweep<SH, LV, HSGD_BF16>), items_grid(nb, 256), dim3(256), 0, s, src.images, \
-                           src.warps, D, src.H, src.W, o, ntx, nty, (int)nb)
+// The sweep of N views x D planes whose workgroups one launch holds.
+static void sweep_part(const float* images, const hsgd_warp* warps, int N, int D, int H, int W, int L, int out_dtype,
+                       bool shift, const PsvOut& o, hipStream_t s) {
+    const int ntx = (int)ceil_div(W, kPsvTW), nty = (int)ceil_div(H, kPsvTH);
+    const dim3 grid((unsigned)((int64_t)ntx * nty * N * D));
+#define HSGD_PSV_LAUNCH(SH, LV)                                                                                \
+    if (out_dtype == HSGD_FP32)                                                                                \
+        hipLaunchKernelGGL((k_plane_sweep<SH, LV, HSGD_FP32>), grid, dim3(256), 0, s, images, warps, D, H, W, o, \
+                           ntx, nty);                                                                          \
+    else                                                                                                       \
+        hipLaunchKernelGGL((k_plane_sweep<SH, LV, HSGD_BF16>), grid, dim3(256), 0, s, images, warps, D, H, W, o, \
+                           ntx, nty)
     switch (L * 2 + (shift ? 1 : 0)) {
         case 2: HSGD_PSV_LAUNCH(false, 1); break;
         case 3: HSGD_PSV_LAUNCH(true, 1); break;
@@ -305,6 +304,27 @@ int launch_plane_sweep(const hsgd_views& src, int D, int L, int out_dtype, void*
         default: HSGD_PSV_LAUNCH(true, 5); break;
     }
 #undef HSGD_PSV_LAUNCH
+}
+
+int launch_plane_sweep(const hsgd_views& src, int D, int L, int out_dtype, void* const* out, hipStream_t s) {
+    const bool shift = (src.flags & HSGD_VIEWS_SHIFT_ONLY) != 0;
+    // A grid dimension holds fewer than 2^32 threads: as many views a launch as fit, or as many
+    // planes of one. (A grid that goes on in y instead cost small sweeps 2%, in every workgroup's
+    // start.)
+    const int64_t most = (int64_t)UINT32_MAX / 256, tiles = ceil_div(src.W, kPsvTW) * ceil_div(src.H, kPsvTH);
+    const int nv = (int)std::min<int64_t>(src.N, std::max<int64_t>(1, most / (tiles * D)));
+    const int nd = nv > 1 ? D : (int)std::min<int64_t>(D, most / tiles);
+    const int one = out_dtype == HSGD_FP32 ? 12 : 6;
+    ProfScope ps(HSGD_K_PSV, s);
+    for (int i = 0; i < src.N; i += nv)
+        for (int z = 0; z < D; z += nd) {
+            PsvOut o{};
+            const size_t at = (size_t)i * D + z;
+            for (int l = 0; l < L; ++l)
+                if (out[l]) o.p[l] = (char*)out[l] + at * (size_t)(src.H >> l) * (size_t)(src.W >> l) * one;
+            sweep_part(src.images + (size_t)i * src.H * src.W * 3, src.warps + at, std::min(nv, src.N - i),
+                       std::min(nd, D - z), src.H, src.W, L, out_dtype, shift, o, s);
+        }
     return (int)hipGetLastError();
 }
 

@@ -78,14 +78,16 @@ def test_translation_gradient():
 
 
 @pytest.mark.parametrize("general", [False, True], ids=["translation", "general"])
-def test_plane_sweep(general):
-    D, h = 64, 5 << 20
+@pytest.mark.parametrize("n,h", [(1, 5 << 20), (3, 3 << 19)], ids=["planes", "views"])
+def test_plane_sweep(n, h, general):
+    """More planes of one view than a launch holds, and more views."""
+    D = 64
     eye = np.eye(3)
-    table = hsgd.psv_warps(eye, eye[None], eye[None], np.zeros((1, 3)), np.linspace(1.0, 2.0, D))
-    images = torch.rand((1, h, W, 3), device="cuda")
+    table = hsgd.psv_warps(eye, np.stack([eye] * n), np.stack([eye] * n), np.zeros((n, 3)), np.linspace(1.0, 2.0, D))
+    images = torch.rand((n, h, W, 3), device="cuda")
     out, = hsgd.hsgd_plane_sweep(images, table.tensor if general else table, D, dtype=torch.bfloat16)
-    want = images[0].to(torch.bfloat16)
-    assert all(torch.equal(plane, want) for plane in out[0])
+    for view, image in zip(out, images.to(torch.bfloat16)):
+        assert all(torch.equal(plane, image) for plane in view)
 
 
 def test_conversion():
