@@ -23,20 +23,23 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 struct PsvOut {
     void* p[kPsvMaxL];
+    bool meet;                     // an FP32 level 1 through the caches
 };
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
-template <typename T>
+template <bool NT, typename T>
 __device__ __forceinline__ void st_stream(T v, T* p) {
-    __builtin_nontemporal_store(v, p);
+    if constexpr (NT) __builtin_nontemporal_store(v, p);
+    else *p = v;
 }
 
 // Store the valid vh x vw pixels of a TH x TW tile, row-major in LDS (FP32), to rows of Wl
 // pixels at dst (the tile's first pixel) in the output type OT. 16-byte runs when every row
 // start is 16-byte aligned (FP32: Wl % 4 == 0; BF16: Wl % 8 == 0 and 16-byte tile rows; vw
 // is then a multiple of the run's pixels too), else one pixel per lane; consecutive lanes
-// write consecutive addresses either way. BF16 rounds to nearest even.
-template <int TH, int TW, int OT>
+// write consecutive addresses either way. BF16 rounds to nearest even. NT: past the caches
+// (through them 768x512x32, 2 tilted views, FP32 took 98 us instead of 72).
+template <int TH, int TW, int OT, bool NT>
 __device__ __forceinline__ void psv_store_tile(const float* __restrict__ s, int vh, int vw, void* __restrict__ dst,
                                                int Wl, int t) {
     if (OT == HSGD_FP32 && (Wl & 3) == 0) {
@@ -48,7 +51,7 @@ __device__ __forceinline__ void psv_store_tile(const float* __restrict__ s, int 
             const int e = e0 + t, r = e / RQ, c = e - r * RQ;
             if ((TH * RQ % 256 == 0 || e < TH * RQ) && r < vh && c < vq) {
                 const float4 q = reinterpret_cast<const float4*>(s)[e];
-                st_stream(f32x4{q.x, q.y, q.z, q.w}, reinterpret_cast<f32x4*>(o + (size_t)r * Wl * 3) + c);
+                st_stream<NT>(f32x4{q.x, q.y, q.z, q.w}, reinterpret_cast<f32x4*>(o + (size_t)r * Wl * 3) + c);
             }
         }
     } else if (OT == HSGD_BF16 && TW * 6 % 16 == 0 && (Wl & 7) == 0) {
@@ -63,7 +66,7 @@ __device__ __forceinline__ void psv_store_tile(const float* __restrict__ s, int 
                 const float4 b = reinterpret_cast<const float4*>(s)[2 * e + 1];
                 const u32x4 q{f32x2_to_bf16x2(a.x, a.y), f32x2_to_bf16x2(a.z, a.w), f32x2_to_bf16x2(b.x, b.y),
                               f32x2_to_bf16x2(b.z, b.w)};
-                st_stream(q, reinterpret_cast<u32x4*>(o + (size_t)r * Wl * 3) + c);
+                st_stream<NT>(q, reinterpret_cast<u32x4*>(o + (size_t)r * Wl * 3) + c);
             }
         }
     } else {
@@ -74,14 +77,14 @@ __device__ __forceinline__ void psv_store_tile(const float* __restrict__ s, int 
                 const size_t at = ((size_t)r * Wl + c) * 3;
                 if (OT == HSGD_FP32) {
                     float* o = reinterpret_cast<float*>(dst) + at;
-                    st_stream(s[3 * e], o);
-                    st_stream(s[3 * e + 1], o + 1);
-                    st_stream(s[3 * e + 2], o + 2);
+                    st_stream<NT>(s[3 * e], o);
+                    st_stream<NT>(s[3 * e + 1], o + 1);
+                    st_stream<NT>(s[3 * e + 2], o + 2);
                 } else {
                     uint16_t* o = reinterpret_cast<uint16_t*>(dst) + at;
-                    st_stream((uint16_t)f32_to_bf16_bits(s[3 * e]), o);
-                    st_stream((uint16_t)f32_to_bf16_bits(s[3 * e + 1]), o + 1);
-                    st_stream((uint16_t)f32_to_bf16_bits(s[3 * e + 2]), o + 2);
+                    st_stream<NT>((uint16_t)f32_to_bf16_bits(s[3 * e]), o);
+                    st_stream<NT>((uint16_t)f32_to_bf16_bits(s[3 * e + 1]), o + 1);
+                    st_stream<NT>((uint16_t)f32_to_bf16_bits(s[3 * e + 2]), o + 2);
                 }
             }
         }
@@ -204,7 +207,14 @@ __device__ __forceinline__ void psv_level(float* __restrict__ s_lv, const PsvOut
         const size_t at = (((size_t)iz * Hl + ty * TH) * Wl + tx * TW) * 3;
         void* dst = OT == HSGD_FP32 ? (void*)(reinterpret_cast<float*>(out.p[l]) + at)
                                     : (void*)(reinterpret_cast<uint16_t*>(out.p[l]) + at);
-        psv_store_tile<TH, TW, OT>(s_lv + OFF, vh0 >> l, vw0 >> l, dst, Wl, t);
+        if (l != 1 || OT == HSGD_BF16 || !out.meet) {
+            psv_store_tile<TH, TW, OT, true>(s_lv + OFF, vh0 >> l, vw0 >> l, dst, Wl, t);
+        } else {
+            // (the clobbers keep the compiler from making one store, plain, of both branches')
+            asm volatile("" ::: "memory");
+            psv_store_tile<TH, TW, OT, false>(s_lv + OFF, vh0 >> l, vw0 >> l, dst, Wl, t);
+            asm volatile("" ::: "memory");
+        }
     }
     if constexpr (l + 1 < L) {
         constexpr int NH = TH / 2, NW = TW / 2, DST = OFF + TH * TW * 3;
@@ -315,10 +325,21 @@ int launch_plane_sweep(const hsgd_views& src, int D, int L, int out_dtype, void*
     const int nv = (int)std::min<int64_t>(src.N, std::max<int64_t>(1, most / (tiles * D)));
     const int nd = nv > 1 ? D : (int)std::min<int64_t>(D, most / tiles);
     const int one = out_dtype == HSGD_FP32 ? 12 : 6;
+    // Level 1 of an FP32 volume with rows of no multiple of 64 bytes, the size of a write request:
+    // a tile ends inside a request in nearly every row, and under general maps, whose workgroups
+    // are many per CU, the parts that two tiles write left L2 one by one. Through the caches they
+    // meet there: 1000x704x24, 4 views, 4 levels 335 us streamed and 282 this way, 308x220x40, 3
+    // views, 3 levels 42.8 and 35.5. What of it is still in L2 at the kernel's end is written back
+    // then, about 1 us, so small volumes stream on (32 MB at level 0, 264x144x16, 4 views: 13.4
+    // and 14.3; 65 MB, 464x244x24, 2 views: 22.4 and 23.3; but 80 MB, 742x562x16, one: 28.8 and
+    // 24.1), and so do translations (272x216x24, 2 views: 13.8 and 15.5).
+    const bool meet = !shift && (src.W / 2) * 12 % 64 != 0 &&
+                      (int64_t)src.N * D * src.H * src.W * 12 >= (int64_t)64 << 20;
     ProfScope ps(HSGD_K_PSV, s);
     for (int i = 0; i < src.N; i += nv)
         for (int z = 0; z < D; z += nd) {
             PsvOut o{};
+            o.meet = meet;
             const size_t at = (size_t)i * D + z;
             for (int l = 0; l < L; ++l)
                 if (out[l]) o.p[l] = (char*)out[l] + at * (size_t)(src.H >> l) * (size_t)(src.W >> l) * one;
