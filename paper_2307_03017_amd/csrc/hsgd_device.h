@@ -78,6 +78,14 @@ __device__ __forceinline__ RowMap shift_row(const hsgd_warp& w, double yd) {
     return RowMap{1.0, 0.0, 0.0, (double)w.ix + (double)w.fx, yd + (double)w.iy + (double)w.fy, 1.0};
 }
 
+// A record read at once: behind the branch on its kind its parts would wait for memory twice.
+__device__ __forceinline__ hsgd_warp read_record(const hsgd_warp* p) {
+    hsgd_warp w = *p;
+    for (int i = 0; i < 9; ++i) asm volatile("" : "+v"(w.G[i]));
+    asm volatile("" : "+v"(w.is_shift), "+v"(w.ix), "+v"(w.iy), "+v"(w.fx), "+v"(w.fy));
+    return w;
+}
+
 // The map of a record as the kernels that tabulate maps use it: they compute positions without
 // a check, so what these cannot be computed from is replaced here, once per plane, by a map
 // that places every pixel where the numbers would. An entry of the first two rows that is no

@@ -403,29 +403,43 @@ __global__ __launch_bounds__(256) void k_compact(const uint64_t* __restrict__ ba
 // General homographies: a wave takes 64 neighbouring rays of one row of one view. Positions
 // are FP64 (~20 instructions a sample: the row's part of the map is tabulated in LDS, the
 // division is a reciprocal estimate with two Newton steps), the taps come through a buffer
-// resource over the plane, and the loads of three planes are in flight while one is blended.
-// Bound by its instructions (about 75 per sample, a quarter of them FP64). One view of
-// 1008x756x32 in BF16: 84.6 us with IEEE divisions, the map re-read per sample and one plane
-// in flight, 70.8 us now.
-template <int DT>
+// resource over the plane, and the loads of one plane (BF16: two) are in flight while one is
+// blended. Bound by its instructions (about 75 per sample, a quarter of them FP64); more planes
+// in flight cost waves and gain nothing: 512x384x32, 8 views, FP32 120 us with three and 115 with
+// one (108 and 72 registers), BF16 107.7, 107.9 with two, 107.6 with one, 954x625x32, one view,
+// BF16 46.7, 47.2, 49.2. No plane past the last is fetched: 980x775x9, 18 views, FP32 410 us with
+// such fetches, 327 without.
+// FEW: of one or two planes. A table and a barrier for a row's one use of each map, and the tiles'
+// order by XCD, cost such a call more than they give: 980x775x1, 18 views, FP32 72 us, without
+// table 65, by view as well 60; 980x775x3 119 in the order by XCD, 126 by view.
+constexpr int kRenderFew = 2;
+template <int DT, bool FEW>
 __global__ __launch_bounds__(kBlock) void k_render(const void* __restrict__ mpi, int D, int H, int W, int N,
                                                    const hsgd_warp* __restrict__ warps,
                                                    const float* __restrict__ images,
                                                    float* __restrict__ out_rgb,
                                                    float* __restrict__ partials, int ntx) {
     constexpr int S = Vox<DT>::kBytes;
-    __shared__ RowMap s_map[kTileH][kMaxD];
+    __shared__ RowMap s_map[kTileH][FEW ? 1 : kMaxD];
     __shared__ float sred[kBlock / 64];
-    const int tile = xcd_tile(flat_block(), flat_blocks());
-    const int view = tile % N, t2 = tile / N;
-    const int x0 = (t2 % ntx) * kTileW, y0 = (t2 / ntx) * kTileH;
-    for (int i = threadIdx.x; i < kTileH * D; i += kBlock) {
+    int tile, view, x0, y0;
+    if constexpr (FEW) {
+        view = blockIdx.z;
+        x0 = blockIdx.x * kTileW, y0 = blockIdx.y * kTileH;
+        tile = (int)((blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x);
+    } else {
+        tile = xcd_tile(flat_block(), flat_blocks());
+        view = tile % N;
+        const int t2 = tile / N;
+        x0 = (t2 % ntx) * kTileW, y0 = (t2 / ntx) * kTileH;
+    }
+    for (int i = threadIdx.x; !FEW && i < kTileH * D; i += kBlock) {
         const int r = i / D, z = i - r * D;
-        const hsgd_warp& w = warps[(size_t)view * D + z];
+        const hsgd_warp w = read_record(warps + (size_t)view * D + z);
         const double yd = (double)(y0 + r);
         s_map[r][z] = w.is_shift ? shift_row(w, yd) : row_map(plane_map(w).g, yd);
     }
-    __syncthreads();
+    if (!FEW) __syncthreads();
     const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int x = x0 + (int)(threadIdx.x & 63), y = y0 + wv;
     const double xd = (double)x;
@@ -435,7 +449,13 @@ __global__ __launch_bounds__(kBlock) void k_render(const void* __restrict__ mpi,
         float fx, fy;
     };
     auto fetch = [&](int z) {
-        MapPos p = map_pos<false>(s_map[wv][z], xd);
+        MapPos p;
+        if constexpr (FEW) {
+            const hsgd_warp& w = warps[(size_t)view * D + z];
+            p = map_pos<true>(w.is_shift ? shift_row(w, (double)y) : row_map(w.G, (double)y), xd);
+        } else {
+            p = map_pos<false>(s_map[wv][z], xd);
+        }
         const TapOffs o = tap_offsets<S>(p, W, H);
         const auto rs = row_rsrc(reinterpret_cast<const char*>(mpi) + (size_t)z * plane_bytes, (int)plane_bytes);
         return Fetched{load_taps<DT>(rs, o), p.fx, p.fy};
@@ -449,14 +469,15 @@ __global__ __launch_bounds__(kBlock) void k_render(const void* __restrict__ mpi,
         c2 = __builtin_fmaf(wgt, s.z, c2);
         T *= 1.0f - s.w;
     };
-    constexpr int kQ = 4;                                   // planes in flight: kQ - 1
+    constexpr int kQ = DT == HSGD_BF16 ? 3 : 2;             // planes in flight: kQ - 1
     Fetched q[kQ];
 #pragma unroll
-    for (int j = 0; j + 1 < kQ; ++j) q[j] = fetch(min(j, D - 1));
+    for (int j = 0; j + 1 < kQ; ++j)
+        if (j < D) q[j] = fetch(j);
     for (int z = 0; z < D; z += kQ) {
 #pragma unroll
         for (int j = 0; j < kQ; ++j) {
-            q[(j + kQ - 1) % kQ] = fetch(min(z + j + kQ - 1, D - 1));
+            if (z + j + kQ - 1 < D) q[(j + kQ - 1) % kQ] = fetch(z + j + kQ - 1);
             if (z + j < D) blend(q[j]);
         }
     }
@@ -2133,9 +2154,18 @@ int launch_render(const hsgd_mpi& m, const hsgd_views& v, float* out_rgb, float*
         const int64_t each = ntx * ceil_div(m.H, kTileH);
         nparts = each * v.N;
         ProfScope ps(HSGD_K_RENDER, s);
-        HSGD_DISPATCH_T(m.dtype, hipLaunchKernelGGL((k_render<DT>), split_grid(each, v.N, kBlock), dim3(kBlock), 0, s,
-                                                    m.rgba, m.D, m.H, m.W, v.N, v.warps, v.images, out_rgb, partials,
-                                                    ntx));
+        const int nty = (int)(each / ntx);
+        const bool few = m.D <= kRenderFew && nty <= 65535;
+        const dim3 grid = few ? dim3((unsigned)ntx, (unsigned)nty, (unsigned)v.N) : split_grid(each, v.N, kBlock);
+#define HSGD_RENDER_GENERAL(FEW)                                                                                     \
+    HSGD_DISPATCH_T(m.dtype, hipLaunchKernelGGL((k_render<DT, FEW>), grid, dim3(kBlock), 0, s, m.rgba, m.D, m.H, m.W, \
+                                                v.N, v.warps, v.images, out_rgb, partials, ntx))
+        if (few) {
+            HSGD_RENDER_GENERAL(true);
+        } else {
+            HSGD_RENDER_GENERAL(false);
+        }
+#undef HSGD_RENDER_GENERAL
     }
     if (out_loss) {
         ProfScope ps(HSGD_K_REDUCE, s);
