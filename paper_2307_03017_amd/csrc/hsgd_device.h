@@ -12,7 +12,7 @@ namespace {
 // quiet NaN: one v_cvt_pk_bf16_f32, checked over every FP32 bit pattern against the integer
 // form (add 0x7fff and the bit above, shift, NaNs apart), whose compare and branch per value
 // were a third of the instructions of a BF16 plane sweep (1008x756x32, 5 tilted views: 419 us
-// a call with it, 367 us without; the finest level transition of a 1920x1080x64 refine: 437
+// a call with it, 367 us without at the time, 345 us since; the finest level transition of a 1920x1080x64 refine: 437
 // and 353 us).
 __device__ __forceinline__ uint32_t f32x2_to_bf16x2(float a, float b) {
     typedef float f32x2 __attribute__((ext_vector_type(2)));

@@ -543,8 +543,10 @@ __device__ __forceinline__ uint64_t plane_bits(int D) { return D == 64 ? ~0ull :
 // 64-byte atomic requests a second whatever they hold, and a float4 added by one lane is
 // four requests instead of one. A wave none of whose cells is selected (about half of them
 // with 4 of 32 planes kept) skips a plane's adjoint and scatter.
-// Bound by the two scans, FP64 positions and four tap loads a sample at 4 waves per SIMD, and
-// in a dense gradient by the atomics. 512x384x32, 4 tilted views, k = 4: 672 us with an IEEE
+// Bound by the two scans, FP64 positions and four tap loads a sample (57% of the vector issue
+// slots of the finest 512x384x32 launch) at 4 waves per SIMD, and in a dense gradient by the
+// atomics. The form for more than 32 planes has 109 KB of LDS in place of 75, so one workgroup
+// per CU and 2 waves per SIMD. 512x384x32, 4 tilted views, k = 4: 672 us with an IEEE
 // division per position and one atomic per lane and channel, 289 us now; the dense gradient
 // of 501x333x24, 2 tilted views: 693 and 198 us. Taps of the next pair in flight behind the
 // scatter, at 3 waves per SIMD or with spills at 4, measured slower (311 and 399 us), and so
@@ -888,15 +890,18 @@ using lds_f32x4 = __attribute__((address_space(3))) f32x4;
 // The tile's forms by plane-count class: the planes whose front-to-back samples it keeps in
 // registers for its back-to-front scan (keep), the leading planes whose transmittance lives
 // in LDS instead of registers (tl), and the waves per SIMD it is compiled for. Small classes
-// (and BF16 at 32 planes) keep nothing and run 6 waves per SIMD (3 workgroups per CU, within
-// 80 registers and 53 KB); the others keep as many samples as the registers of 4 waves per
+// (and BF16 at 32 planes) keep nothing and are compiled for 6 waves per SIMD (3 workgroups per
+// CU, within 80 registers and 53 KB; 8 and 16 planes need no more than 62 registers and 38 KB,
+// so 4 workgroups are resident); the others keep as many samples as the registers of 4 waves per
 // SIMD hold without spills once 2 workgroups' 160 KB of LDS are filled with transmittances.
 // The forms are within a few percent of each other (BF16, 24 planes, 512 x 384, 4 views:
-// 85 us against 88 at 6 waves; 48 planes: 172 us against 179 without kept samples): the
-// kernel is bound by issuing its vector instructions, 105 per wave, plane and pair of scans
-// (BF16; 62 of them the interpolation, the compositing and the adjoint), so what counts is to
-// run no more planes than the MPI has (see maxd_class) and no more instructions per plane.
-// With separate weight tables for every row, the shift's fractions beside them and LDS
+// 85 us against 88 at 6 waves; 48 planes: 172 us against 179 without kept samples). No one
+// limit holds the kernel: its finest launch fills 53% of the vector and 40% of the scalar issue
+// slots at 512 x 384 x 32 in FP32 (26% of the waves' time waiting) and 68% and 46% at 1920 x
+// 1080 x 64 in BF16 (34% waiting). Of what the code spends it is the planes run and the vector
+// instructions per plane that could be cut (105 per wave, plane and pair of scans in BF16, 62 of
+// them the interpolation, the compositing and the adjoint), so it runs no more planes than the
+// MPI has (see maxd_class). With separate weight tables for every row, the shift's fractions beside them and LDS
 // addresses rebuilt per plane it was 119: FP32, 512 x 384 x 32, 4 views 119 us, now 108 (46 and
 // 23 us one and two levels below, from 51 and 26); BF16, 1920 x 1080 x 64, 8 views 4442 us, now
 // 4343.
@@ -2229,6 +2234,9 @@ int launch_grad_step(const hsgd_mpi& m, const hsgd_views& v, const uint64_t* mas
 #define HSGD_GRAD_GENERAL(MD)                                                                                       \
     HSGD_DISPATCH_T(m.dtype, hipLaunchKernelGGL((k_grad<DT, MD>), grid, dim3(kGenThreads), 0, s, m.rgba, m.D, m.H, m.W, \
                                                 v.N, v.warps, im, dimg, mask, kcap, inv_n, slots, parts, ntx))
+        // The LDS of the transmittances sets the residency: two workgroups per CU up to 32 planes,
+        // one above. A step of 512x384, 4 tilted views, k = 4 in FP32 takes 427 us with 33 planes
+        // and 656 with 64 (736 and 932 before the kernel had its present form).
         if (m.D <= 32) {
             HSGD_GRAD_GENERAL(32);
         } else {
